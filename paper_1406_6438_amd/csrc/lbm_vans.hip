@@ -157,9 +157,6 @@ int scratch_address(void **out)
 #ifndef LBM_VANS_TB3_ROWS16
 #define LBM_VANS_TB3_ROWS16 24
 #endif
-#ifndef LBM_VANS_TB_REUSE
-#define LBM_VANS_TB_REUSE 3
-#endif
 
 constexpr int TX = 64;      // nodes per row segment: one wavefront
 constexpr int NW = LBM_VANS_NW;      // wavefronts per block
@@ -282,6 +279,10 @@ struct Phys {
     R ca, cb;       // Ergun drag prefactors (0 under the constant law; see drag_coeffs)
     R ka, kb;       // constant-K drag prefactors (0 under the Ergun law)
     R scale, inv_scale;  // FP16 storage scale 2^s and 2^-s (1 otherwise)
+    // Constants of the FP32 multi-step passes' node update (collide_w): omega (om, rounded
+    // so that its companions are exact), 1 - omega and half of it, omega / 2, 2 - omega,
+    // G / 2 and rho0 / 2.
+    R om, omc, omc2, omh, P2, Ghx, Ghy, c2;
     // Open x ends: a population entering across x = 0 (x = Lx-1) is the
     // equilibrium of a reservoir with the node's porosity, density rho_in
     // (rho_out) and velocity (u_in, 0) ((u_out, 0)); as a deviation from the
@@ -323,6 +324,9 @@ __device__ __forceinline__ R sqroot(R x)
     else
         return sqrt(x);
 }
+
+// One fused multiply-add, whatever the contraction setting.
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // Darcy and Forchheimer coefficients a = eps^2 nu / K, b = eps^3 F_eps / sqrt(K)
 // of the drag law, one branch-free form for both closures:
@@ -784,6 +788,209 @@ __device__ __forceinline__ void update_node(R d[9], const R (*t)[W], int lyy, in
                                                wyp, open_l, open_r, ph, acc, count);
 }
 
+// ---- node update of the FP32 multi-step passes --------------------------------------
+// Their steps carry weighted deviations g_i = d_i / w_i, the same scale in every direction,
+// and update opposite directions i, j as a pair, on their sum and difference.  With
+// omega = 1/tau, P = 1 - omega/2 and h = omega S/2 u + P T the collision (see collide) is
+//   g*_i   = (1 - omega) g_i + base_i + anti_i,
+//   base_i = K0 + 9 (e_i.u) (e_i.h)                  even under e_i -> -e_i,
+//   anti_i = 3 e_i.(omega S/2 u + h)                 odd,
+//   K0     = omega (dS - 3/2 S u.u) - 3 P u.T = omega dS - 3 u.h:
+// no weight multiplies a direction, u.u and u.T never appear, and the even terms of all
+// directions come from u_x h_x, u_y h_y and the cross term u_x h_y + u_y h_x.  T enters as
+// T = 2 (q - drag/2 u) with q = (Q + G)/2, which the velocity needs anyway.
+// The constants are chosen so that a fluid at rest in a porosity gradient stays at rest to
+// rounding: the link shift and q share the factor 1/72, and 1 - omega and 2 - omega are
+// exact companions of omega (a mismatch of 1e-7 between them acts as a constant force:
+// with the weights folded into omega / 36 and P / 36 the velocity error against 64 bits
+// after 100 steps was 4..12e-6; as written it is 1.6..3.8e-6, with the one-step sweep's
+// form of the update in these passes 1.8..4.9e-6).
+// The passes issue 13% fewer vector instructions for it (4096^2 box, four steps: 1.65e8 ->
+// 1.43e8 wave instructions a launch, 91% of the SIMDs' cycles busy) and the four-step pass
+// then runs at the rate of its memory pattern (a copy kernel with the same strips and halo
+// rows: 341 us, the pass 320).  GLUPS, the one-step sweep's form / this one: 4096^2 box
+// 201 / 207, 2048^2 162 / 172, 1024^2 (12 rows) 136 / 147, 4096^2 channel 178 / 182,
+// closed 1003 x 751 box 88 / 93 (6 rows 93 / 103), 1024^2 with walls in y 115 / 127,
+// 16-member ensemble 160 / 168.
+
+// The porosity-only terms of a node's update (the same at every step): 1/eps, a sixth of
+// the lattice gradient of eps, and half of the drag coefficients a and b.
+struct NodeEps {
+    float ie, gx, gy, ha, hb;
+};
+
+// The porosity around one node: eps(x) and the differences D[i] = eps(x + e_i) - eps(x),
+// zero when x + e_i lies behind a wall (a bounced value never leaves its node).  Behind a
+// wall the window t holds mirror images, so that the axis differences are zero of
+// themselves.
+struct LinkEps {
+    float e0;
+    float D[9];
+};
+
+__device__ __forceinline__ LinkEps link_eps(const float (&t)[3][3], bool wxm, bool wxp,
+                                            bool wym, bool wyp)
+{
+    LinkEps P;
+    P.e0 = t[1][1];
+    P.D[0] = 0.0f;
+    P.D[1] = t[1][2] - P.e0;
+    P.D[2] = t[2][1] - P.e0;
+    P.D[3] = t[1][0] - P.e0;
+    P.D[4] = t[0][1] - P.e0;
+    P.D[5] = (wxp || wyp) ? 0.0f : t[2][2] - P.e0;
+    P.D[6] = (wxm || wyp) ? 0.0f : t[2][0] - P.e0;
+    P.D[7] = (wxm || wym) ? 0.0f : t[0][0] - P.e0;
+    P.D[8] = (wxp || wym) ? 0.0f : t[0][2] - P.e0;
+    return P;
+}
+
+__device__ __forceinline__ NodeEps node_eps(const float (&t)[3][3], const Phys<float> &ph)
+{
+    const float e0 = t[1][1];
+    const float d1 = t[2][2] - t[0][0], d2 = t[0][2] - t[2][0];
+    float a, b;
+    NodeEps q;
+    q.ie = rcp(e0);
+    q.gx = (1.0f / 72.0f) * fma_(4.0f, t[1][2] - t[1][0], d1 + d2);
+    q.gy = (1.0f / 72.0f) * fma_(4.0f, t[2][1] - t[0][1], d1 - d2);
+    drag_coeffs(ph, e0, q.ie, a, b);
+    q.ha = 0.5f * a;
+    q.hb = 0.5f * b;
+    return q;
+}
+
+// Incoming values set by the boundaries rather than by a stored slot (boundary_inflow,
+// on weighted deviations).
+__device__ __forceinline__ void inflow_w(float g[9], float e0, bool open_l, bool open_r,
+                                         bool wym, bool wyp, const Phys<float> &ph)
+{
+    if (ph.inout) open_l = open_r = false;   // their values are in the stored slots
+    if (open_l) {
+        g[1] = e0 * (9.0f * ph.rin[1]);
+        if (!wym) g[5] = e0 * (36.0f * ph.rin[5]);
+        if (!wyp) g[8] = e0 * (36.0f * ph.rin[8]);
+    }
+    if (open_r) {
+        g[3] = e0 * (9.0f * ph.rout[3]);
+        if (!wym) g[6] = e0 * (36.0f * ph.rout[6]);
+        if (!wyp) g[7] = e0 * (36.0f * ph.rout[7]);
+    }
+    if (wym) {
+        const float b = 36.0f * ph.wb;
+        g[5] = fma_(e0, b, g[5]);
+        g[6] = fma_(-e0, b, g[6]);
+    }
+    if (wyp) {
+        const float b = 36.0f * ph.wt;
+        g[8] = fma_(e0, b, g[8]);
+        g[7] = fma_(-e0, b, g[7]);
+    }
+}
+
+// Velocity inlet / pressure outlet (inout_ends, on weighted deviations).
+__device__ __forceinline__ void inout_ends_w(float g[9], float dS, float S, float ux, float uy,
+                                             float e0, bool open_l, bool open_r, bool wym,
+                                             bool wyp, const Phys<float> &ph)
+{
+    if (open_l) {
+        g[3] = fma_(S, 9.0f * ph.rin[1], dS);
+        if (!wym) g[7] = fma_(S, 36.0f * ph.rin[5], dS);
+        if (!wyp) g[6] = fma_(S, 36.0f * ph.rin[8], dS);
+    }
+    if (open_r) {
+        const float uu = 1.5f * fma_(ux, ux, uy * uy);
+        auto q = [&](float eu) {   // P(u) - 1 for e.u = eu
+            return fma_(fma_(4.5f, eu, 3.0f), eu, -uu);
+        };
+        const float a = e0 * ph.rho_out, b = e0 * ph.dro;
+        g[1] = fma_(a, q(-ux), b);
+        if (!wym) g[8] = fma_(a, q(uy - ux), b);
+        if (!wyp) g[5] = fma_(a, q(-ux - uy), b);
+    }
+}
+
+// Everything a node does after its gather, on weighted deviations in place: moments and
+// velocity, collision, and the shift of each outgoing value along its link.  On entry g
+// holds the incoming populations' deviations from the node's own rest state (boundary
+// values included), on exit the post-collision values less a share of the rest state's
+// difference to the node each travels to (none for a value that bounces back): STORE, half
+// of it, for values that go to memory (link midpoint), which leave as plain deviations;
+// else all of it, for values the pass hands to its next step in registers (the
+// destination's own rest state: the next step then has nothing to add).
+template <bool STORE>
+__device__ __forceinline__ void collide_w(float g[9], const LinkEps &P, const NodeEps &q,
+                                          bool wym, bool wyp, bool open_l, bool open_r,
+                                          const Phys<float> &ph)
+{
+#pragma clang fp contract(off)
+    const float w = 1.0f / 36.0f;
+    const float s13 = g[1] + g[3], a13 = g[1] - g[3], s24 = g[2] + g[4], a24 = g[2] - g[4];
+    const float s57 = g[5] + g[7], a57 = g[5] - g[7], s68 = g[6] + g[8], a68 = g[6] - g[8];
+    const float dS = w * fma_(16.0f, g[0], fma_(4.0f, s13 + s24, s57 + s68));
+    const float mx = fma_(4.0f, a13, a57 - a68), my = fma_(4.0f, a24, a57 + a68);   // 36 m
+    const float S = fma_(P.e0, ph.rho0, dS);
+    const float rho = S * q.ie;
+    const float qx = fma_(rho, q.gx, ph.Ghx), qy = fma_(rho, q.gy, ph.Ghy);
+    const float Vx = fma_(w, mx, qx), Vy = fma_(w, my, qy);
+    // u = k V, k = 2 / (A + sqrt(A^2 + 2 b |V|)), A = eps rho + a/2; |u| = k |V|
+    const float A = S + q.ha;
+    const float t = q.hb * sqroot(fma_(Vx, Vx, Vy * Vy));
+    const float Ah = 0.5f * A;
+    const float k = rcp(Ah + sqroot(fma_(Ah, Ah, t)));
+    const float ux = k * Vx, uy = k * Vy;
+    const float dh = fma_(k, t, q.ha);            // half the drag
+    const float hS = ph.omh * S;
+    const float hx = fma_(hS, ux, ph.P2 * fma_(-dh, ux, qx));
+    const float hy = fma_(hS, uy, ph.P2 * fma_(-dh, uy, qy));
+    const float X = ux * hx, Y = uy * hy, XY = X + Y;
+    const float K0 = fma_(-3.0f, XY, ph.om * dS);
+    const float bs = fma_(9.0f, XY, K0), C = fma_(ux, hy, uy * hx);
+    const float tx = 3.0f * fma_(hS, ux, hx), ty = 3.0f * fma_(hS, uy, hy);
+    g[0] = fma_(ph.omc, g[0], K0);
+    const float c = STORE ? -ph.c2 : -ph.rho0;
+    auto pair = [&](int i, int j, float s, float a, float base, float anti) {
+        const float e = fma_(ph.omc2, s, base), o = fma_(ph.omc2, a, anti);
+        g[i] = fma_(c, P.D[i], e + o);
+        g[j] = fma_(c, P.D[j], e - o);
+    };
+    pair(1, 3, s13, a13, fma_(9.0f, X, K0), tx);
+    pair(2, 4, s24, a24, fma_(9.0f, Y, K0), ty);
+    pair(5, 7, s57, a57, fma_(9.0f, C, bs), tx + ty);
+    pair(6, 8, s68, a68, fma_(-9.0f, C, bs), ty - tx);
+    if (ph.inout && (open_l || open_r))
+        inout_ends_w(g, dS, S, ux, uy, P.e0, open_l, open_r, wym, wyp, ph);
+    if constexpr (STORE) {
+        // d = w g with the weight's rounding error (the same for all: 1/9 in FP32 is 7e-9
+        // too large) taken out, or every pass would scale the state by it
+        constexpr float lo = static_cast<float>(1.0 / 9.0 - static_cast<double>(1.0f / 9.0f));
+#pragma unroll
+        for (int i = 0; i < 9; i++) {
+            const float s = i == 0 ? 4.0f : (i < 5 ? 1.0f : 0.25f);
+            g[i] = fma_(g[i], s / 9.0f, g[i] * (s * lo));
+        }
+    }
+}
+
+// Incoming weighted deviations from the stored deviations v: the stored value of direction
+// i at x came from x - e_i and is shifted by the rest state at the link midpoint, so half
+// the porosity difference to the source comes on top.
+__device__ __forceinline__ void incoming_w(float g[9], const float v[9], const LinkEps &P,
+                                           bool wym, bool wyp, bool open_l, bool open_r,
+                                           const Phys<float> &ph)
+{
+    g[0] = 2.25f * v[0];
+    g[1] = fma_(9.0f, v[1], ph.c2 * P.D[3]);
+    g[2] = fma_(9.0f, v[2], ph.c2 * P.D[4]);
+    g[3] = fma_(9.0f, v[3], ph.c2 * P.D[1]);
+    g[4] = fma_(9.0f, v[4], ph.c2 * P.D[2]);
+    g[5] = fma_(36.0f, v[5], ph.c2 * P.D[7]);
+    g[6] = fma_(36.0f, v[6], ph.c2 * P.D[8]);
+    g[7] = fma_(36.0f, v[7], ph.c2 * P.D[5]);
+    g[8] = fma_(36.0f, v[8], ph.c2 * P.D[6]);
+    inflow_w(g, P.e0, open_l, open_r, wym, wyp, ph);
+}
+
 // ---- vector sweep: V consecutive nodes per lane, full-width loads and stores
 
 template <typename S, int V>
@@ -1174,20 +1381,6 @@ __device__ __forceinline__ void store_plane(__amdgpu_buffer_rsrc_t r, unsigned o
 // and its result goes unused.
 constexpr int TB_AHEAD = LBM_VANS_TB_AHEAD;
 
-// Whether the three-step pass computes the porosity-only terms of a row once and
-// carries them to the row's later steps (six values for each of three rows in
-// flight; LBM_VANS_TB_REUSE 0: never, 1: FP16 storage, 2: both, 3: FP32).
-// Measured (GLUPS, 4096^2 FP32 / open-walls / ensemble, 8192^2 FP16 / open-walls):
-// without 156.1 / 147.0 / 129.7, 209.3 / 169.6; with 156.7 / 150.3 / 133.6,
-// 184.8 / 176.7 -- the FP16 periodic pass loses, so FP32 only.
-template <typename S, int NS>
-constexpr bool tb_reuse()
-{
-    constexpr bool f16 = std::is_same_v<S, _Float16>;
-    return NS >= 3 && (LBM_VANS_TB_REUSE == 2 || (LBM_VANS_TB_REUSE == 1 && f16) ||
-                       (LBM_VANS_TB_REUSE == 3 && !f16));
-}
-
 // Rows the gathers run ahead: TB_AHEAD, except one for the three-step passes in
 // FP16 and for those with x ends or y walls, whose windows and boundary rules take
 // the registers (GLUPS, two rows ahead / one: FP16 8192^2 box 211 / 191 in an older
@@ -1199,14 +1392,38 @@ constexpr int tb_ahead()
     return (NS >= 3 && (std::is_same_v<S, _Float16> || BX != 0 || WY)) ? 1 : TB_AHEAD;
 }
 
-// Most waves per SIMD the compiler schedules the three-step kernel for: 2 for the
-// periodic FP32 pass (its schedule for 2 waves keeps the gathers of a row together
-// and beats the 3 waves its registers would allow: 4096^2 box 163.4 against 156.7
-// GLUPS), else no bound (the FP16 pass at 2: 197 against 242).
-template <typename S, int BX, bool WY>
-constexpr int tb3_max_waves()
+// Waves per SIMD the multi-step kernels are compiled for, least and most (registers: 512
+// over the waves).  FP32, measured as GLUPS:
+// * periodic: two (the schedule for two keeps the gathers of a row together; 4096^2 box at
+//   2 / 3: four steps 211 / 198, three steps 163 / 154; 1024^2 in 12 rows 147 / 147);
+// * with x ends or y walls, three steps: three, also where the compiler would take a few
+//   registers too many for it (closed 1003 x 751 box at 2 / 3: 12 rows 88 / 93, 6 rows 94 /
+//   103; 2048 x 1024 channel, 12 rows 147 / 163); four steps: at least two (the batched
+//   kernel with its three paths would fall to one: 16-member ensemble 117 / 168).
+// FP16: no bound (at most 2: 197 against 242).
+template <typename S, int BX, bool WY, int NS>
+constexpr int tb_min_waves()
 {
-    return (std::is_same_v<S, float> && BX == 0 && !WY) ? 2 : 8;
+    if (!std::is_same_v<S, float>) return 1;
+    return NS == 4 ? 2 : ((BX != 0 || WY) ? 3 : 1);
+}
+
+template <typename S, int BX, bool WY>
+constexpr int tb_max_waves()
+{
+    return std::is_same_v<S, float> && BX == 0 && !WY ? 2 : 8;
+}
+
+// Whether the waves of odd chunks walk their rows bottom to top: the halo rows that two
+// neighbouring chunks both read are then read by both at about the same time and come from
+// HBM once (FP32 four-step pass of the periodic box, the largest lattices: 4096^2 207 / 211
+// GLUPS, copy kernel with its access pattern 341 / 325 us; the channels and the batch do
+// not gain, 4096^2 channel 182 / 181, ensemble 168 / 162).  Mirrored in y the update is the
+// same arithmetic, to the bit.
+template <typename S, int NS, int BX, bool WY>
+constexpr bool tb_turns()
+{
+    return std::is_same_v<S, float> && NS == 4 && BX == 0 && !WY;
 }
 
 // f(integral_constant<int, J>) for J = 0, 1, ... while it returns true: code
@@ -1228,7 +1445,7 @@ __device__ __forceinline__ void static_while(F &&f)
 template <typename S, typename R, int BX, bool WY, int NS, int NR, int BXA = BX>
 __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict__ fout,
                                         const R *__restrict__ eps, const Geo &g,
-                                        const Phys<R> &ph, int strip, int chunk, int res_a)
+                                        const Phys<R> &ph0, int strip, int chunk, int res_a)
 {
     static_assert(std::is_same_v<R, float>, "the multi-step pass computes in FP32");
     static_assert(NS >= 2 && NS <= 4, "two to four steps per pass");
@@ -1261,6 +1478,15 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
     }
     const bool out_ok = lane >= H && lane < TX - H && xu >= 0 && xu < g.Lx;
     const int y0 = chunk * NR;
+    // odd chunks walked bottom to top (tb_turns)
+    const bool up = tb_turns<S, NS, BXA, WY>() && (chunk & 1);
+    Phys<R> ph = ph0;
+    if (up) {
+        ph.Ghy = -ph.Ghy;
+        ph.wb = ph0.wt;
+        ph.wt = ph0.wb;
+    }
+    const int ya = up ? y0 + NR - 1 : y0, yd = up ? -1 : 1;   // window row a: ya + yd a
     const unsigned pb = static_cast<unsigned>(g.pitch) * SB;   // bytes per state row
     const unsigned pe = static_cast<unsigned>(g.pitch) * EB;   // bytes per porosity row
     const unsigned xb = x * SB, xmb = xm * SB, xpb = xp * SB;
@@ -1270,9 +1496,13 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
     const unsigned plane_b = static_cast<unsigned>(g.plane) * SB;
 #pragma unroll
     for (int i = 0; i < 9; i++) {
-        Fb[i] = reinterpret_cast<const char *>(fin + i * g.plane);
-        Gr[i] = plane_rsrc(reinterpret_cast<char *>(fout + i * g.plane), plane_b);
+        // upwards, the directions with a y component trade places
+        const int mir[9] = {0, 1, 4, 3, 2, 8, 7, 6, 5};
+        const long long po = (up ? mir[i] : i) * g.plane;
+        Fb[i] = reinterpret_cast<const char *>(fin + po);
+        Gr[i] = plane_rsrc(reinterpret_cast<char *>(fout + po), plane_b);
     }
+    const int ylo = up ? g.Ly - 1 : 0, yhi = up ? 0 : g.Ly - 1;   // first, last row
     const char *Eb = reinterpret_cast<const char *>(eps);
     auto ld = [&](const char *base, unsigned off) -> R {
         return load_cached<S, R>(reinterpret_cast<const S *>(base + off), ph.inv_scale);
@@ -1293,7 +1523,7 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
     // porosity rows y0-H-1+k (k = 0 .. NE-1), columns x-1 .. x+1
     R E[NE][3];
     auto eps_row = [&](int k) {
-        const unsigned o = __umul24(static_cast<unsigned>(row_of(y0 - H - 1 + k)), pe);
+        const unsigned o = __umul24(static_cast<unsigned>(row_of(ya + yd * (k - H - 1))), pe);
         E[k][0] = load_global(reinterpret_cast<const R *>(Eb + (o + xme)));
         E[k][1] = load_global(reinterpret_cast<const R *>(Eb + (o + xe)));
         E[k][2] = load_global(reinterpret_cast<const R *>(Eb + (o + xpe)));
@@ -1306,11 +1536,16 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
     // lattice, their results are never read, and the output rows past the last
     // row are not stored.  The chunk's code thus has no branch on its rows.
     auto issue = [&](int a) {
-        const int yy = row_of(y0 + a);
-        bool wym = false, wyp = false;
-        int ym = yy - 1, yp = yy + 1;
-        if (ym < 0) { if (WY) { wym = true; ym = yy; } else ym = g.Ly - 1; }
-        if (yp >= g.Ly) { if (WY) { wyp = true; yp = yy; } else yp = 0; }
+        const int yy = row_of(ya + yd * a);
+        int ym = yy - yd, yp = yy + yd;
+        const bool wym = WY && yy == ylo, wyp = WY && yy == yhi;
+        if (WY) {
+            ym = wym ? yy : ym;
+            yp = wyp ? yy : yp;
+        } else {
+            ym = yy == ylo ? yhi : ym;
+            yp = yy == yhi ? ylo : yp;
+        }
         qm[a + H] = wym;
         qp[a + H] = wyp;
         const unsigned r0 = __umul24(static_cast<unsigned>(yy), pb);
@@ -1349,35 +1584,38 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
         }
     };
     const bool oa = BX == 2 && res_a;        // reservoirs in the first step
-    // the porosity-only terms of the row whose porosity tile starts at E[k]
-    constexpr bool REUSE = tb_reuse<S, NS>();
-    EpsTerms<R> T[REUSE ? NE : 1];
+    // FP32: weighted deviations, and the porosity-only terms of the row whose porosity
+    // window starts at E[k] computed once, by the row's first step (in FP16 keeping them
+    // costs a wave per SIMD: 8192^2 box 209 -> 185 GLUPS)
+    constexpr bool WT = std::is_same_v<S, float>;
+    NodeEps T[WT ? NE : 1];
     auto finish = [&](int a) {
         const int k = a + H;                  // porosity rows of row y0+a: E[k .. k+2]
         const R t[3][3] = {{E[k][0], E[k][1], E[k][2]},
                            {E[k + 1][0], E[k + 1][1], E[k + 1][2]},
                            {E[k + 2][0], E[k + 2][1], E[k + 2][2]}};
-#pragma unroll
-        for (int i = 0; i < 9; i++) P1[k][i] = Q[k][i];
-        if constexpr (REUSE) {
-            const PorNb<R> P = porosity_nb<R, 3>(t, 1, 1, wxm, wxp, qm[k], qp[k]);
-            T[k] = eps_terms<R>(P.e0, P.gex, P.gey, ph);
-            update_node_q<R, false, false, false>(P1[k], P, T[k], qm[k], qp[k], oa && wxm,
-                                                  oa && wxp, ph, nullptr, false);
+        if constexpr (WT) {
+            const LinkEps P = link_eps(t, wxm, wxp, qm[k], qp[k]);
+            T[k] = node_eps(t, ph);
+            incoming_w(P1[k], Q[k], P, qm[k], qp[k], oa && wxm, oa && wxp, ph);
+            collide_w<false>(P1[k], P, T[k], qm[k], qp[k], oa && wxm, oa && wxp, ph);
         } else {
+#pragma unroll
+            for (int i = 0; i < 9; i++) P1[k][i] = Q[k][i];
             update_node<R, 3, false, false, false>(P1[k], t, 1, 1, wxm, wxp, qm[k], qp[k],
                                                    oa && wxm, oa && wxp, ph, nullptr, false);
         }
     };
     // a later step at row y from the previous step's rows y-1 (A0), y (A1), y+1
-    // (A2) of this wave (unshifted deviations), porosity rows E[k .. k+2]; a row
+    // (A2) of this wave (FP32: weighted deviations from this row's rest state; FP16: the
+    // source's own unshifted deviations), porosity rows E[k .. k+2]; a row
     // behind a y wall is never read, and the reservoirs are active (the step starts
     // from n + 1 >= 1).  LAST: the step's values go to memory (shifted to their
     // link midpoints); else they stay in registers for the next step.
     auto pull = [&](auto last_c, R (&d)[9], const R *A0, const R *A1, const R *A2, int y,
                     int k) {
         constexpr bool LAST = decltype(last_c)::value;
-        const bool wym = WY && y == 0, wyp = WY && y == g.Ly - 1;
+        const bool wym = WY && y == ylo, wyp = WY && y == yhi;
         const R s1 = lane_from_below(A1[1]), s3 = lane_from_above(A1[3]);
         d[0] = A1[0];
         d[1] = wxm ? A1[3] : s1;
@@ -1405,11 +1643,10 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
         const R t[3][3] = {{E[k][0], E[k][1], E[k][2]},
                            {E[k + 1][0], E[k + 1][1], E[k + 1][2]},
                            {E[k + 2][0], E[k + 2][1], E[k + 2][2]}};
-        if constexpr (REUSE) {
-            // the row's first step computed its porosity-only terms
-            const PorNb<R> P = porosity_nb<R, 3>(t, 1, 1, wxm, wxp, wym, wyp);
-            update_node_q<R, false, true, LAST>(d, P, T[k], wym, wyp, BX == 2 && wxm,
-                                                BX == 2 && wxp, ph, nullptr, false);
+        if constexpr (WT) {
+            const LinkEps P = link_eps(t, wxm, wxp, wym, wyp);
+            inflow_w(d, P.e0, BX == 2 && wxm, BX == 2 && wxp, wym, wyp, ph);
+            collide_w<LAST>(d, P, T[k], wym, wyp, BX == 2 && wxm, BX == 2 && wxp, ph);
         } else {
             update_node<R, 3, false, true, LAST>(d, t, 1, 1, wxm, wxp, wym, wyp, BX == 2 && wxm,
                                                  BX == 2 && wxp, ph, nullptr, false);
@@ -1423,27 +1660,28 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
     R P3[NS == 4 ? NR + 2 : 1][9];
     auto middle = [&](int b) {
         if constexpr (NS >= 3) {
-            pull(std::false_type{}, P2[b + O2], P1[b - 1 + H], P1[b + H], P1[b + 1 + H], y0 + b,
+            pull(std::false_type{}, P2[b + O2], P1[b - 1 + H], P1[b + H], P1[b + 1 + H], ya + yd * b,
                  b + H);
         }
     };
     auto middle2 = [&](int c) {
         if constexpr (NS == 4) {
             pull(std::false_type{}, P3[c + 1], P2[c - 1 + O2], P2[c + O2], P2[c + 1 + O2],
-                 y0 + c, c + H);
+                 ya + yd * c, c + H);
         }
     };
     // last step at output row y0+j, stored
     auto last = [&](int j) {
         R d[9];
         if constexpr (NS == 4)
-            pull(std::true_type{}, d, P3[j], P3[j + 1], P3[j + 2], y0 + j, j + H);
+            pull(std::true_type{}, d, P3[j], P3[j + 1], P3[j + 2], ya + yd * j, j + H);
         else if constexpr (NS == 3)
-            pull(std::true_type{}, d, P2[j], P2[j + 1], P2[j + 2], y0 + j, j + H);
+            pull(std::true_type{}, d, P2[j], P2[j + 1], P2[j + 2], ya + yd * j, j + H);
         else
-            pull(std::true_type{}, d, P1[j - 1 + H], P1[j + H], P1[j + 1 + H], y0 + j, j + H);
-        const bool row_ok = y0 + j < g.Ly;   // uniform: the last chunk's rows past the end
-        const unsigned c = (out_ok && row_ok) ? __umul24(static_cast<unsigned>(y0 + j), pb) + xb
+            pull(std::true_type{}, d, P1[j - 1 + H], P1[j + H], P1[j + 1 + H], ya + yd * j, j + H);
+        const int y = ya + yd * j;
+        const bool row_ok = y < g.Ly;        // uniform: the last chunk's rows past the end
+        const unsigned c = (out_ok && row_ok) ? __umul24(static_cast<unsigned>(y), pb) + xb
                                               : TB_NO_STORE;
 #pragma unroll
         for (int i = 0; i < 9; i++) store_plane<S, R>(Gr[i], c, d[i], ph.scale);
@@ -1557,7 +1795,8 @@ __global__ __launch_bounds__(NTHREADS) void k_sweep_tb2(const S *__restrict__ fi
 // Three steps per launch, in chunks of NR rows.
 template <typename S, typename R, int BX, bool WY, int NR>
 __global__ __launch_bounds__(NTHREADS)
-__attribute__((amdgpu_waves_per_eu(1, tb3_max_waves<S, BX, WY>()))) void k_sweep_tb3(const S *__restrict__ fin,
+__attribute__((amdgpu_waves_per_eu(tb_min_waves<S, BX, WY, 3>(),
+                                   tb_max_waves<S, BX, WY>()))) void k_sweep_tb3(const S *__restrict__ fin,
                                                         S *__restrict__ fout,
                                                         const R *__restrict__ eps, Geo g,
                                                         Phys<R> ph, int nstrips, int nchunks,
@@ -1569,7 +1808,8 @@ __attribute__((amdgpu_waves_per_eu(1, tb3_max_waves<S, BX, WY>()))) void k_sweep
 // Four steps per launch (FP32 storage), in chunks of NR rows.
 template <typename S, typename R, int BX, bool WY, int NR>
 __global__ __launch_bounds__(NTHREADS)
-__attribute__((amdgpu_waves_per_eu(1, tb3_max_waves<S, BX, WY>()))) void k_sweep_tb4(const S *__restrict__ fin,
+__attribute__((amdgpu_waves_per_eu(tb_min_waves<S, BX, WY, 4>(),
+                                   tb_max_waves<S, BX, WY>()))) void k_sweep_tb4(const S *__restrict__ fin,
                                                         S *__restrict__ fout,
                                                         const R *__restrict__ eps, Geo g,
                                                         Phys<R> ph, int nstrips, int nchunks,
@@ -2488,7 +2728,8 @@ __global__ __launch_bounds__(NTHREADS) void k_batch_tb2(const Member<R> *__restr
 // height, 2: the tall one).
 template <typename S, typename R, int BX, bool WY, int NR>
 __global__ __launch_bounds__(NTHREADS)
-__attribute__((amdgpu_waves_per_eu(1, tb3_max_waves<S, BX, WY>()))) void k_batch_tb3(
+__attribute__((amdgpu_waves_per_eu(tb_min_waves<S, BX, WY, 3>(),
+                                   tb_max_waves<S, BX, WY>()))) void k_batch_tb3(
     const Member<R> *__restrict__ M, const int *__restrict__ wmap, int nwaves, int src, int dst,
     int res_a)
 {
@@ -2499,7 +2740,8 @@ __attribute__((amdgpu_waves_per_eu(1, tb3_max_waves<S, BX, WY>()))) void k_batch
 // Four steps of every member (FP32 storage; wave list 3).
 template <typename S, typename R, int BX, bool WY>
 __global__ __launch_bounds__(NTHREADS)
-__attribute__((amdgpu_waves_per_eu(1, tb3_max_waves<S, BX, WY>()))) void k_batch_tb4(
+__attribute__((amdgpu_waves_per_eu(tb_min_waves<S, BX, WY, 4>(),
+                                   tb_max_waves<S, BX, WY>()))) void k_batch_tb4(
     const Member<R> *__restrict__ M, const int *__restrict__ wmap, int nwaves, int src, int dst,
     int res_a)
 {
@@ -2777,6 +3019,20 @@ Phys<R> make_phys(const lbm_vans_params *p)
         ph.rin[i] = cx[i] > 0 ? static_cast<R>(wt[i] * (p->rho_in * pin - rho_ref)) : R(0);
         ph.rout[i] = cx[i] < 0 ? static_cast<R>(wt[i] * (p->rho_out * pout - rho_ref)) : R(0);
     }
+    // omega of the multi-step passes; in FP32 rounded to a multiple of 2^-23 (its own spacing from 1
+    // on), so that 1 - omega and 2 - omega hold no rounding of their own
+    double om = 1.0 / p->tau;
+    if (std::is_same_v<R, float>)
+        om = om >= 0.5 ? std::nearbyint(om * 8388608.0) / 8388608.0
+                       : static_cast<double>(static_cast<float>(om));
+    ph.om = static_cast<R>(om);
+    ph.omc = static_cast<R>(1.0 - om);
+    ph.omc2 = static_cast<R>(0.5 * (1.0 - om));
+    ph.omh = static_cast<R>(0.5 * om);
+    ph.P2 = static_cast<R>(2.0 - om);
+    ph.Ghx = static_cast<R>(0.5 * p->G[0]);
+    ph.Ghy = static_cast<R>(0.5 * p->G[1]);
+    ph.c2 = R(0.5) * ph.rho0;
     ph.reservoir = 0;
     ph.inout = p->bc_x == LBM_BC_INOUT;
     ph.dro = R(0);
@@ -2984,38 +3240,39 @@ int tb4_resident(int bx, bool wy, bool batch, long long *out)
 // per pass): box 512^2 53.0 / 76.3 (40.7), 1024 x 512 102.3 / 104.9, 768^2 115.5 /
 // 117.0, 1024^2 137.1 / 120.7, 2048 x 1024 178.6 / 156.4; channel 512 x 256 16.9 /
 // 27.0 (31.7), 1024 x 512 65.6 / 79.8, 1024^2 96.6 / 101.9, 2048 x 1024 147.4 / 137.1.
-// FP32: 24-row chunks when the lattice has at least 0.9 times as many of their waves
-// as the chip holds at once (28-row chunks, which recompute fewer halo rows, with four
-// times as many), else 12-row chunks when those have at least half of what the chip
-// holds, else 6-row chunks; three steps in the chosen height when its waves are at
-// least a fifth of what the chip holds, else pairs when the two-step pass has >= 2048
-// waves, else one step.
-// FP16 (one height): three steps when the lattice has 0.7 times as many waves as
-// the chip holds, else pairs or one step as above.  Four steps per pass (FP32, 24-row
-// chunks, 58-column strips) when that pass has at least as many waves as the chip
-// holds and the chunk height is automatic: GLUPS at three / four steps, periodic box
-// 2048^2 160.8 / 163.5, 4096^2 162.8 / 198.0, 8192^2 164.9 / 208.5.
-// Open x ends (channels), whose waves clear of the ends skip the x-end rules: GLUPS at
-// three steps in 24 / 12 / 6-row chunks and four steps, 4096^2 159.6 / 151.8 / - /
-// 175.6; 2048^2 127.3 / 146.5 / 144.7 / 124.4; 2048 x 1024 - / 146.2 / 150.0 / -;
-// 1024^2 - / 91.0 / 109.4 / -; 1024 x 512 - / - / 78.7 / -: four steps with three
-// times the resident waves, 24-row chunks with four times, 12-row chunks with 1.5
-// times, else 6-row chunks.
-constexpr int QUAD_FILL_10 = 10;            // four steps: waves >= resident
-constexpr int TALL_FILL = 4;                // tall chunks: waves >= 4 x resident
-constexpr int DEFAULT_FILL_10 = 9;          // FP32 24-row chunks: waves >= 0.9 x resident
-constexpr int HALF_FILL_10 = 5;             // FP32 12-row chunks: waves >= 0.5 x resident,
-constexpr int SHORT_FILL_10 = 2;            // else 6-row chunks: waves >= 0.2 x resident
-constexpr int TRIPLE_FILL_10 = 7;           // FP16, or an explicit height: >= 0.7 x
-// open x ends (the channels): their waves clear of the ends take the pass without
-// x-end rules, and the heights and the fourth step pay off only with more waves
-constexpr int OPEN_QUAD_FILL_10 = 30;
-constexpr int OPEN_DEFAULT_FILL_10 = 40;
-constexpr int OPEN_HALF_FILL_10 = 15;
+// (Figures of the kernels' earlier node update; the current ones below.)
+// The choice counts a pass's waves against those the chip holds of its kernel at once
+// (Fill): the taller the chunk, the fewer halo rows are recomputed and the more waves it
+// needs.  FP32: four steps per pass (24-row chunks, 58-column strips, automatic heights
+// only), else three in 28-, 24-, 12- or 6-row chunks, else pairs when the two-step pass
+// has >= 2048 waves, else one step.  FP16 (one height): three steps when the lattice has
+// 0.7 times as many waves as the chip holds, else pairs or one step as above.  Channels
+// with open x ends at three steps in 24 / 12 / 6-row chunks and four steps: 4096^2 159.6 /
+// 151.8 / - / 175.6; 2048^2 127.3 / 146.5 / 144.7 / 124.4; 1024^2 - / 91.0 / 109.4 / -.
+// In percent of the waves the chip holds of the kernel (tb3_resident, tb4_resident).  The
+// periodic FP32 kernels' registers fit four (three steps) and three (four steps) waves per
+// SIMD, the others three and two; measured at the same counts of waves, 2048^2 box three
+// steps 24 rows / four steps 160 / 174 GLUPS, 1024^2 12 / 6 rows 147 / 133, closed 1003 x
+// 751 box 12 / 6 rows 93 / 103, 2048 x 1024 open channel 12 / 6 rows 163 / 157.
+struct Fill {
+    int quad, tall, tall24, half;   // four steps; 28-, 24- and 12-row chunks (else 6 rows)
+    int least;                      // three steps at all, in 12 or 6 rows
+};
 
-bool tall_auto(long long tall_waves, long long resident)
+Fill fill_of(int bx, bool wy)
 {
-    return tall_waves >= TALL_FILL * resident;
+    // open x ends (the channels): their waves clear of the ends take the pass without
+    // x-end rules, and the heights and the fourth step pay off only with more waves
+    if (bx == 2) return {300, 400, 400, 90, 13};
+    if (bx == 0 && !wy) return {67, 300, 68, 37, 15};
+    return {100, 400, 90, 50, bx == 0 ? 20 : 13};
+}
+
+constexpr int TRIPLE_FILL = 70;   // three steps: FP16, or an explicit chunk height
+
+bool tall_auto(long long tall_waves, long long resident, const Fill &f)
+{
+    return 100 * tall_waves >= f.tall * resident;
 }
 
 int choose_passes(lbm_vans_handle *h)
@@ -3029,9 +3286,9 @@ int choose_passes(lbm_vans_handle *h)
     const bool wy = h->g.wall_y;
     long long res = 0;
     int rc;
-    // the fill a three-step pass in rows3-row chunks needs (tenths of the waves
-    // the chip holds of its kernel)
-    int fill10 = TRIPLE_FILL_10;
+    // the fill a three-step pass in rows3-row chunks needs
+    const Fill f = fill_of(bx, wy);
+    int fill = TRIPLE_FILL;
     if (f16) {
         h->rows3 = tb_rows<_Float16, 3>();
     } else if (p->pass_rows != 0) {
@@ -3045,25 +3302,23 @@ int choose_passes(lbm_vans_handle *h)
         long long res12 = 0;
         rc = tb3_resident(p->storage, bx, wy, LBM_VANS_TB3_SHORT32, false, &res12);
         if (rc) return rc;
-        const int fill24 = bx == 2 ? OPEN_DEFAULT_FILL_10 : DEFAULT_FILL_10;
-        const int fill12 = bx == 2 ? OPEN_HALF_FILL_10 : HALF_FILL_10;
-        if (tall_auto(waves_of(p->Lx, p->Ly, 3, LBM_VANS_TB3_TALL32), res)) {
+        if (tall_auto(waves_of(p->Lx, p->Ly, 3, LBM_VANS_TB3_TALL32), res, f)) {
             h->rows3 = LBM_VANS_TB3_TALL32;
-        } else if (10 * waves_of(p->Lx, p->Ly, 3, tb_rows<float, 3>()) >= fill24 * res24 ||
+        } else if (100 * waves_of(p->Lx, p->Ly, 3, tb_rows<float, 3>()) >= f.tall24 * res24 ||
                    !multi_rows_ok(p->Ly, wy, 3, LBM_VANS_TB3_SHORT32)) {
             h->rows3 = tb_rows<float, 3>();
-            fill10 = DEFAULT_FILL_10;
-        } else if (10 * waves_of(p->Lx, p->Ly, 3, LBM_VANS_TB3_SHORT32) >= fill12 * res12) {
+            fill = f.tall24;
+        } else if (100 * waves_of(p->Lx, p->Ly, 3, LBM_VANS_TB3_SHORT32) >= f.half * res12) {
             h->rows3 = LBM_VANS_TB3_SHORT32;
-            fill10 = SHORT_FILL_10;
+            fill = f.least;
         } else {
             h->rows3 = LBM_VANS_TB3_TINY32;
-            fill10 = SHORT_FILL_10;
+            fill = f.least;
         }
     }
     rc = tb3_resident(p->storage, bx, wy, h->rows3, false, &res);
     if (rc) return rc;
-    if (10 * waves_of(p->Lx, p->Ly, 3, h->rows3) >= fill10 * res)
+    if (100 * waves_of(p->Lx, p->Ly, 3, h->rows3) >= fill * res)
         h->auto_pass = 3;
     else if (waves_of(p->Lx, p->Ly, 2, tb2_rows_of(p->storage)) >= 2048)
         h->auto_pass = 2;
@@ -3071,8 +3326,7 @@ int choose_passes(lbm_vans_handle *h)
         long long res4 = 0;
         rc = tb4_resident(bx, wy, false, &res4);
         if (rc) return rc;
-        const int fill4 = bx == 2 ? OPEN_QUAD_FILL_10 : QUAD_FILL_10;
-        if (10 * waves_of(p->Lx, p->Ly, 4, tb_rows<float, 4>()) >= fill4 * res4) h->auto_pass = 4;
+        if (100 * waves_of(p->Lx, p->Ly, 4, tb_rows<float, 4>()) >= f.quad * res4) h->auto_pass = 4;
     }
     return LBM_VANS_OK;
 }
@@ -3849,7 +4103,7 @@ bool batch_tall(const lbm_vans_batch *b)
 {
     if (b->storage != LBM_F32_SHIFTED) return false;
     if (b->cfg.pass_rows != 0) return b->cfg.pass_rows == LBM_VANS_TB3_TALL32;
-    return tall_auto(b->nwaves[2], b->tall_resident);
+    return tall_auto(b->nwaves[2], b->tall_resident, {0, 400, 0, 0, 0});
 }
 
 void drop_graphs(lbm_vans_batch *b)
@@ -4032,7 +4286,7 @@ int batch_max_pass(const lbm_vans_batch *b)
     if (b->storage == LBM_F64 || !b->multi_ok || b->nwaves[0] == 0) return 1;
     int m = b->cfg.steps_per_pass;
     if (m == 0)
-        m = b->multi4_ok && b->cfg.pass_rows == 0 && 10LL * b->nwaves[3] >= QUAD_FILL_10 * b->quad_resident
+        m = b->multi4_ok && b->cfg.pass_rows == 0 && b->nwaves[3] >= b->quad_resident
                 ? 4
                 : 3;
     return m == 4 && !b->multi4_ok ? 3 : m;
