@@ -158,7 +158,11 @@ typedef struct lbm_vans_params {
                               fewer steps);
                               the intermediate states stay in registers (so FP16
                               storage rounds once per pass) and each pass recomputes
-                              its chunk's halo.                                       */
+                              its chunk's halo.  Where 0 leads to one step per pass
+                              (also with diag_every > 0, between the states recorded),
+                              FP64 and FP32 lattices take up to six single steps per
+                              launch, on tiles that exchange the states of every step
+                              as stored (the same bits however steps are grouped).    */
     int32_t pass_rows;     /* output rows per chunk (wave) of the three-step pass:
                               0 = automatic; LBM_F32_SHIFTED: 6, 12, 24 or 28
                               (automatic: the tallest whose waves still fill the GPU;

@@ -327,6 +327,7 @@ __device__ __forceinline__ R sqroot(R x)
 
 // One fused multiply-add, whatever the contraction setting.
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 // Darcy and Forchheimer coefficients a = eps^2 nu / K, b = eps^3 F_eps / sqrt(K)
 // of the drag law, one branch-free form for both closures:
@@ -383,14 +384,14 @@ __device__ __forceinline__ EpsTerms<R> eps_terms(R eps, R gex, R gey, const Phys
     return q;
 }
 
-template <typename R>
+template <typename R, bool FUSED = false>
 __device__ __forceinline__ NodeFwd<R> node_forward_q(const R d[9], const EpsTerms<R> &q,
                                                      const Phys<R> &ph)
 {
     NodeFwd<R> F;
     Node<R> &N = F.N;
     N.dS = ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7])) + d[8];
-    N.S = q.e * ph.rho0 + N.dS;
+    N.S = FUSED ? fma_(q.e, ph.rho0, N.dS) : q.e * ph.rho0 + N.dS;
     N.mx = (d[1] - d[3]) + (d[5] - d[6]) + (d[8] - d[7]);
     N.my = (d[2] - d[4]) + (d[5] + d[6]) - (d[7] + d[8]);
     F.ie = q.ie;
@@ -442,9 +443,12 @@ __device__ constexpr int CY[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 // opposite directions shares them.  The stored value is d*_i - w_i de_i with
 // de_i = (rho0/2) (eps(x + e_i) - eps(x)), the link-midpoint shift (0 when the
 // value bounces back).
-template <typename R>
+// value bounces back).  FUSED: the shift is one fused operation (hr D_i, hr = rho0 / 2), so
+// that where the porosity does not change from step to step its products do not become
+// roundings of their own in some steps and not in others.
+template <typename R, bool FUSED = false>
 __device__ __forceinline__ void collide(R d[9], const Node<R> &N, const Phys<R> &ph,
-                                        const R de[9])
+                                        const R de[9], R hr, const R D[9])
 {
     const R om = ph.omega, omc = R(1) - ph.omega, P = ph.pre;
     const R uu = N.ux * N.ux + N.uy * N.uy;
@@ -454,17 +458,18 @@ __device__ __forceinline__ void collide(R d[9], const Node<R> &N, const Phys<R> 
     const R Ax = R(3) * N.ux, Ay = R(3) * N.uy;
     const R pBx = R(3) * P * N.Tx, pBy = R(3) * P * N.Ty;
     const R w0 = R(4) / R(9), w1 = R(1) / R(9), w2 = R(1) / R(36);
-    auto pair = [&](R &di, R &dj, R A, R pB, R w, R dei, R dej) {
+    auto less = [&](R v, int k) { return FUSED ? fma_(-hr, D[k], v) : v - de[k]; };
+    auto pair = [&](R &di, R &dj, R A, R pB, R w, int i, int j) {
         const R base = K0 + A * (hS * A + pB);
         const R anti = oS * A + pB;
-        di = omc * di + w * ((base + anti) - dei);
-        dj = omc * dj + w * ((base - anti) - dej);
+        di = omc * di + w * less(base + anti, i);
+        dj = omc * dj + w * less(base - anti, j);
     };
     d[0] = omc * d[0] + w0 * K0;
-    pair(d[1], d[3], Ax, pBx, w1, de[1], de[3]);
-    pair(d[2], d[4], Ay, pBy, w1, de[2], de[4]);
-    pair(d[5], d[7], Ax + Ay, pBx + pBy, w2, de[5], de[7]);
-    pair(d[6], d[8], Ay - Ax, pBy - pBx, w2, de[6], de[8]);
+    pair(d[1], d[3], Ax, pBx, w1, 1, 3);
+    pair(d[2], d[4], Ay, pBy, w1, 2, 4);
+    pair(d[5], d[7], Ax + Ay, pBx + pBy, w2, 5, 7);
+    pair(d[6], d[8], Ay - Ax, pBy - pBx, w2, 6, 8);
 }
 
 // Neighbour coordinates of node (x, y) along both axes with wall flags.
@@ -674,19 +679,18 @@ __device__ __forceinline__ PorNb<R> porosity_nb(const R (*t)[W], int lyy, int lx
 // incoming values are the source's own deviations (post-collision values a
 // multi-step pass hands over in registers, never shifted), which take the whole
 // difference rho0 w_i (eps(x - e_i) - eps(x)).
-template <typename R, bool FULL = false>
+template <typename R, bool FULL = false, bool FUSED = false>
 __device__ __forceinline__ void unshift_incoming(R d[9], const PorNb<R> &P, R rho0)
 {
     const R hf = FULL ? R(1) : R(0.5);
     const R h1 = hf * rho0 * (R(1) / R(9)), h2 = hf * rho0 * (R(1) / R(36));
-    d[1] += h1 * P.D[3];
-    d[2] += h1 * P.D[4];
-    d[3] += h1 * P.D[1];
-    d[4] += h1 * P.D[2];
-    d[5] += h2 * P.D[7];
-    d[6] += h2 * P.D[8];
-    d[7] += h2 * P.D[5];
-    d[8] += h2 * P.D[6];
+    const int opp[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
+#pragma unroll
+    for (int i = 1; i < 9; i++) {
+        const R h = i < 5 ? h1 : h2;
+        if constexpr (FUSED) d[i] = fma_(h, P.D[opp[i]], d[i]);
+        else d[i] += h * P.D[opp[i]];
+    }
 }
 
 // Incoming values set by the boundaries rather than by a stored slot: the
@@ -758,14 +762,15 @@ __device__ __forceinline__ void inout_ends(R d[9], const Node<R> &N, R e0, bool 
 // sources (see unshift_incoming); OUT_SHIFT: shift the outgoing values to their
 // link midpoints (values that go to memory), else leave them as this node's own
 // deviations (values a multi-step pass keeps in registers for its next step).
-template <typename R, bool DIAG, bool IN_FULL = false, bool OUT_SHIFT = true>
+template <typename R, bool DIAG, bool IN_FULL = false, bool OUT_SHIFT = true,
+          bool FUSED = false>
 __device__ __forceinline__ void update_node_q(R d[9], const PorNb<R> &P, const EpsTerms<R> &q,
                                               bool wym, bool wyp, bool open_l, bool open_r,
                                               const Phys<R> &ph, double *acc, bool count)
 {
     boundary_inflow<R>(d, P.e0, open_l, open_r, wym, wyp, ph);
-    unshift_incoming<R, IN_FULL>(d, P, ph.rho0);
-    Node<R> N = node_forward_q<R>(d, q, ph).N;
+    unshift_incoming<R, IN_FULL, FUSED>(d, P, ph.rho0);
+    Node<R> N = node_forward_q<R, FUSED>(d, q, ph).N;
     if constexpr (DIAG) {
         if (count) accumulate<R>(acc, N);
     }
@@ -773,7 +778,7 @@ __device__ __forceinline__ void update_node_q(R d[9], const PorNb<R> &P, const E
     R de[9];
 #pragma unroll
     for (int i = 0; i < 9; i++) de[i] = OUT_SHIFT ? hr * P.D[i] : R(0);
-    collide<R>(d, N, ph, de);
+    collide<R, FUSED>(d, N, ph, de, R(0.5) * ph.rho0, P.D);
     if (ph.inout && (open_l || open_r)) inout_ends<R>(d, N, P.e0, open_l, open_r, wym, wyp, ph);
 }
 
@@ -1818,6 +1823,121 @@ __attribute__((amdgpu_waves_per_eu(tb_min_waves<S, BX, WY, 4>(),
     sweep_multi<S, R, BX, WY, 4, NR>(fin, fout, eps, g, ph, nstrips, nchunks, res_a);
 }
 
+// ---- several steps per launch on a tile held by one workgroup -----------------------
+constexpr int TILE_H = 16;   // rows of a tile (columns: 16 or 32)
+
+// One node per thread: a workgroup takes a tile of TW x TH nodes through ns steps and
+// stores its inner nodes, those at least ns - 1 from the tile's edge (each step leaves one
+// ring of nodes whose neighbours are missing).  The first step gathers from memory; the
+// later ones exchange the outgoing values, as they would have been stored, through LDS (two
+// buffers in turn, one barrier a step): the states are the same to the bit however steps
+// are grouped into launches.  What depends on the porosity alone is computed once per
+// launch.  FP64 and FP32 storage (S == R: nothing is rounded on the way to memory).  Bound
+// by the latency of a step's chain of operations where a tile has its compute unit to
+// itself (80 x 80 FP64: 1.0 us of the 1.34 us per step), else by the vector instructions of
+// the nodes it recomputes (2048^2 FP64, three steps: 1.6 times the lattice's nodes, 63 us a
+// step against 104 of the one-step sweep, which moves 152 B per node at 6.1 TB/s).
+// all: when not 0, the state of every step s is stored, at fout + s all (elements).
+template <typename S, typename R, int BX, bool WY, int TW, int TH>
+__global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tile(const S *__restrict__ fin,
+                                                       S *__restrict__ fout,
+                                                       const R *__restrict__ eps, Geo g,
+                                                       Phys<R> ph, int ns, int ntx,
+                                                       long long all)
+{
+    constexpr bool WX = BX != 0;
+    __shared__ R buf[2][8][TH * TW];
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    const int h = ns - 1, tid = threadIdx.x, tx = tid % TW, ty = tid / TW;
+    const int xu = (t % ntx) * (TW - 2 * h) - h + tx;   // unwrapped node
+    const int yu = (t / ntx) * (TH - 2 * h) - h + ty;
+    // wrapped (once, unless the axis is shorter than a tile), or clamped behind an end
+    auto inside = [](int v, int L, bool wall, int T) {
+        if (wall) return min(max(v, 0), L - 1);
+        if (L < T) v %= L;                     // uniform
+        return v < 0 ? v + L : (v >= L ? v - L : v);
+    };
+    const int x = inside(xu, g.Lx, WX, TW), y = inside(yu, g.Ly, WY, TH);
+    const bool out = tx >= h && tx < TW - h && ty >= h && ty < TH - h && xu < g.Lx && yu < g.Ly;
+    const bool wxm = WX && x == 0, wxp = WX && x == g.Lx - 1;
+    const bool wym = WY && y == 0, wyp = WY && y == g.Ly - 1;
+    // neighbours, the node itself behind an end: byte offsets of a row's columns and of the
+    // rows within a plane (the host keeps a plane's bytes below 2^31)
+    const unsigned lx = static_cast<unsigned>(g.Lx), pitch = static_cast<unsigned>(g.pitch);
+    const unsigned c0 = x, cm = x == 0 ? (WX ? 0u : lx - 1) : x - 1u;
+    const unsigned cp = x == g.Lx - 1 ? (WX ? lx - 1 : 0u) : x + 1u;
+    const unsigned q0 = y * pitch, qm = (y == 0 ? (WY ? 0u : g.Ly - 1u) : y - 1u) * pitch;
+    const unsigned qp = (y == g.Ly - 1 ? (WY ? g.Ly - 1u : 0u) : y + 1u) * pitch;
+    auto ld = [&](int i, unsigned k) {         // a uniform plane base, a 32-bit offset
+        const char *plane = reinterpret_cast<const char *>(fin + i * g.plane);
+        return load_global(reinterpret_cast<const S *>(plane + k * static_cast<unsigned>(sizeof(S))));
+    };
+    auto lde = [&](unsigned k) {
+        return load_global(reinterpret_cast<const R *>(reinterpret_cast<const char *>(eps) +
+                                                       k * static_cast<unsigned>(sizeof(R))));
+    };
+    S v[9] = {ld(0, q0 + c0), ld(1, q0 + cm), ld(2, qm + c0), ld(3, q0 + cp), ld(4, qp + c0),
+              ld(5, qm + cm), ld(6, qm + cp), ld(7, qp + cp), ld(8, qp + cm)};
+    const R e[3][3] = {{lde(qm + cm), lde(qm + c0), lde(qm + cp)},
+                       {lde(q0 + cm), lde(q0 + c0), lde(q0 + cp)},
+                       {lde(qp + cm), lde(qp + c0), lde(qp + cp)}};
+    // behind an end: the node's own opposite value
+    auto bounce = [&](auto *f, const auto *own) {
+        f[1] = wxm ? own[3] : f[1];
+        f[2] = wym ? own[4] : f[2];
+        f[3] = wxp ? own[1] : f[3];
+        f[4] = wyp ? own[2] : f[4];
+        f[5] = (wxm || wym) ? own[7] : f[5];
+        f[6] = (wxp || wym) ? own[8] : f[6];
+        f[7] = (wxp || wyp) ? own[5] : f[7];
+        f[8] = (wxm || wyp) ? own[6] : f[8];
+    };
+    if ((WX || WY) && (wxm || wxp || wym || wyp)) {
+        S own[9];
+#pragma unroll
+        for (int i = 1; i < 9; i++) own[i] = ld(i, q0 + c0);
+        bounce(v, own);
+    }
+    R d[9];
+#pragma unroll
+    for (int i = 0; i < 9; i++) d[i] = decode_pop<S, R>(v[i], ph.inv_scale);
+    const PorNb<R> P = porosity_nb<R, 3>(e, 1, 1, wxm, wxp, wym, wyp);
+    const EpsTerms<R> q = eps_terms<R>(P.e0, P.gex, P.gey, ph);
+    bool ores = BX == 2 && ph.reservoir;
+    ph.reservoir = 1;                          // the later steps start from n + 1 >= 1
+    const int xm = max(tx - 1, 0), xp = min(tx + 1, TW - 1);
+    const int r0 = ty * TW, rm = max(ty - 1, 0) * TW, rp = min(ty + 1, TH - 1) * TW;
+    // one copy of the step for every s: the same roundings in each
+#pragma clang loop unroll(disable)
+    for (int s = 0;; s++) {
+        update_node_q<R, false, false, true, true>(d, P, q, wym, wyp, ores && wxm, ores && wxp, ph,
+                                                   nullptr, false);
+        ores = BX == 2;
+        if (all || s == h) {
+            if (out) {
+                S *o = fout + s * all + (q0 + c0);
+#pragma unroll
+                for (int i = 0; i < 9; i++) o[i * g.plane] = d[i];
+            }
+            if (s == h) return;                // uniform over the workgroup
+        }
+        R(*b)[TH * TW] = buf[s & 1];
+#pragma unroll
+        for (int i = 1; i < 9; i++) b[i - 1][tid] = d[i];
+        __syncthreads();
+        const R own[9] = {d[0], d[1], d[2], d[3], d[4], d[5], d[6], d[7], d[8]};
+        d[1] = b[0][r0 + xm];
+        d[2] = b[1][rm + tx];
+        d[3] = b[2][r0 + xp];
+        d[4] = b[3][rp + tx];
+        d[5] = b[4][rm + xm];
+        d[6] = b[5][rm + xp];
+        d[7] = b[6][rp + xp];
+        d[8] = b[7][rp + xm];
+        if (WX || WY) bounce(d, own);
+    }
+}
+
 // Macroscopic fields of the current state (no collision, no store of
 // populations) plus the FP64 diagnostics partials.
 template <typename S, typename R>
@@ -2815,10 +2935,13 @@ struct lbm_vans_handle {
     int64_t nrec;           // diagnostics records written
     int rows3;              // rows per chunk of the three-step pass
     int auto_pass;          // automatic most steps per pass
+    int tile_w, tile_ns;    // tile width and most steps per launch of the tile kernel
+                            // (choose_tile); tile_ns 0: this lattice does not take it
+    bool tile_on;           // lbm_vans_step takes the tile kernel
     void *scratch;          // device address of the library-held gradient workspace on the
                             // handle's device (lbm_vans_grad_static)
     // Step graphs of small lattices (launch-bound: fewer sweep tiles than twice the
-    // compute units): lbm_vans_step replays GRAPH_STEPS steps from state slot 0 / 1
+    // compute units): lbm_vans_step replays graph_steps steps from state slot 0 / 1
     // as one captured graph, captured on first use on a private stream.
     bool use_graphs;
     hipStream_t cap;
@@ -3331,6 +3454,54 @@ int choose_passes(lbm_vans_handle *h)
     return LBM_VANS_OK;
 }
 
+// Most steps per pass of lbm_vans_step: one in runs that record diagnostics, whose records
+// do not change with the rounding of the multi-step passes.
+int max_pass(const lbm_vans_handle *h);
+int step_pass(const lbm_vans_handle *h) { return h->p.diag_every > 0 ? 1 : max_pass(h); }
+
+// Tile kernel: FP64 and FP32 lattices, unless the caller asked for a kernel of another kind
+// (steps_per_pass, pass_rows, sweep_vec).  lbm_vans_step takes it where a pass takes one
+// step (FP64; FP32 lattices too small for the multi-step passes; runs that record
+// diagnostics), and in place of the FP32 three-step pass in 6- and 12-row chunks up to 2^20
+// nodes, whose few waves each walk their rows one after another.  Not in FP16, whose
+// one-step launches would have to agree with it to the bit (a last bit moves whole FP16
+// roundings).  Small lattices are bound by the latency of a launch and of a step's chain of
+// dependent operations: the most steps per launch for which every tile still has a compute
+// unit of its own; larger ones by their bytes and the work of the discarded rings: three
+// steps of 32 x 16 tiles.  Microseconds per step:
+// * FP64, one-step sweep / 16 x 16 / 32 x 16 tiles (steps per launch): 80 x 80 4.18 / 1.34
+//   (6) / 1.56 (8), 64 x 32 3.96 / 1.30 (6) / 1.48 (8), 300 x 200 channel 4.58 / 2.59 (3) /
+//   2.31 (4), 512^2 7.88 / 4.93 (3) / 4.84 (3), 1024^2 29.2 / 15.1 (2) / 14.0 (3), 2048^2
+//   103.7 / 67.9 (3) / 63.2 (3) (32 x 32 tiles 66.3);
+// * FP32, three-step pass in the better of 6 and 12 rows / 32 x 16 tiles: channels 250 x 131
+//   4.60 (one-step sweep 3.80) / 1.36 (5), 400 x 200 4.69 / 1.76, 640 x 320 4.87 / 2.81, 1024
+//   x 512 6.75 / 5.15, 1024^2 9.19 / 8.76; walls in y alone 512^2 3.77 / 2.94, 1024^2 7.79 /
+//   7.51, 2048^2 26.7 / 31.6.
+void choose_tile(lbm_vans_handle *h, int ncu)
+{
+    const lbm_vans_params *p = &h->p;
+    h->tile_ns = 0;
+    h->tile_on = false;
+    if (p->storage == LBM_F16_SHIFTED || p->steps_per_pass != 0 || p->pass_rows != 0 ||
+        p->sweep_vec != 0 || h->g.plane * elem_bytes(p->storage) >= (1LL << 31))
+        return;
+    auto tiles = [&](int w, int ns) {
+        const int ow = w - 2 * (ns - 1), oh = TILE_H - 2 * (ns - 1);
+        return static_cast<long long>((p->Lx + ow - 1) / ow) * ((p->Ly + oh - 1) / oh);
+    };
+    const int m = step_pass(h);
+    h->tile_on = m == 1 || (m == 3 && h->rows3 <= LBM_VANS_TB3_SHORT32 &&
+                            static_cast<long long>(p->Lx) * p->Ly <= (1LL << 20));
+    h->tile_w = 32;
+    h->tile_ns = 3;
+    if (m == 1 && tiles(16, 6) <= ncu) {
+        h->tile_w = 16;
+        h->tile_ns = 6;
+    } else if (m == 1) {
+        h->tile_ns = tiles(32, 5) <= ncu ? 5 : (tiles(32, 4) <= ncu ? 4 : 3);
+    }
+}
+
 // Most time steps one pass may take: 2 or 3 with the multi-step passes (FP32 and
 // FP16 storage, lattices they can run), else 1.
 int max_pass(const lbm_vans_handle *h)
@@ -3422,6 +3593,60 @@ int launch_sweep_ptrs(lbm_vans_handle *h, const void *src, void *dst, int64_t n,
 int launch_sweep(lbm_vans_handle *h, bool diag)
 {
     return launch_sweep_ptrs(h, h->buf[h->cur], h->buf[1 - h->cur], h->n, diag);
+}
+
+// ns steps (1 .. tile_ns) of the tile kernel from the state n in src; the last state goes
+// to dst, or with all != 0 (bytes) the state of every step s to dst + s all.
+int launch_tile(lbm_vans_handle *h, const void *src, void *dst, int64_t n, int ns, size_t all,
+                hipStream_t st)
+{
+    return with_types(h->p.storage, [&](auto *sp, auto *rp) -> int {
+        using S = std::remove_pointer_t<decltype(sp)>;
+        using R = std::remove_pointer_t<decltype(rp)>;
+        if constexpr (std::is_same_v<S, _Float16>) {
+            return fail(LBM_VANS_EINVAL, "the tile kernel needs FP64 or FP32 storage");
+        } else {
+            Phys<R> ph = make_phys<R>(&h->p);
+            ph.reservoir = res_on(&h->p, n);
+            const int ow = h->tile_w - 2 * (ns - 1), oh = TILE_H - 2 * (ns - 1);
+            const int ntx = (h->p.Lx + ow - 1) / ow, nty = (h->p.Ly + oh - 1) / oh;
+            with_bxwy(h->g.open_x ? 2 : (h->g.wall_x ? 1 : 0), h->g.wall_y, [&](auto bxc, auto wyc) {
+                constexpr int BXV = decltype(bxc)::value;
+                constexpr bool WYV = decltype(wyc)::value;
+                auto run = [&](auto ker, int tw) {
+                    hipLaunchKernelGGL(ker, dim3(ntx * nty), dim3(tw * TILE_H), 0, st,
+                                       (const S *)src, (S *)dst, (const R *)h->eps, h->g, ph, ns,
+                                       ntx, (long long)(all / sizeof(S)));
+                };
+                if (h->tile_w == 16) run(k_sweep_tile<S, R, BXV, WYV, 16, TILE_H>, 16);
+                else run(k_sweep_tile<S, R, BXV, WYV, 32, TILE_H>, 32);
+            });
+            return check_launch("k_sweep_tile");
+        }
+    });
+}
+
+// Steps the next launch takes of `steps` that remain (no diagnostics among them).
+int next_pass(const lbm_vans_handle *h, int64_t steps)
+{
+    const int m = step_pass(h);
+    return static_cast<int>(std::min<int64_t>(h->tile_on ? h->tile_ns : m, steps));
+}
+
+// One launch of m steps (next_pass) from the handle's current state into its other buffer;
+// the handle's state slot and step count advance.
+int launch_pass(lbm_vans_handle *h, int m)
+{
+    const void *src = h->buf[h->cur];
+    void *dst = h->buf[1 - h->cur];
+    int rc;
+    if (h->tile_on) rc = launch_tile(h, src, dst, h->n, m, 0, h->stream);
+    else if (m >= 2) rc = launch_multi(h, src, dst, m);
+    else rc = launch_sweep(h, false);
+    if (rc) return rc;
+    h->cur = 1 - h->cur;
+    h->n += m;
+    return LBM_VANS_OK;
 }
 
 int launch_finalize(lbm_vans_handle *h, double *out, int nparts, bool add_mass0, double step)
@@ -3517,6 +3742,7 @@ int lbm_vans_init(const lbm_vans_params *p, const void *eps, void *work, size_t 
         return LBM_VANS_OK;
     });
     if (!rc) rc = choose_passes(h);
+    if (!rc) choose_tile(h, ncu);
     if (rc) {
         delete h;
         return rc;
@@ -3543,8 +3769,13 @@ int lbm_vans_init(const lbm_vans_params *p, const void *eps, void *work, size_t 
 
 namespace {
 
-// Steps per replay of a handle's step graph.
-constexpr int GRAPH_STEPS = 32;
+// Steps per replay of a handle's step graph: an even number of full launches, at least 32
+// steps (so a replay leaves the state slot as it was).
+int graph_steps(const lbm_vans_handle *h)
+{
+    const int per = next_pass(h, 32);
+    return per * (((32 + per - 1) / per + 1) & ~1);
+}
 
 // The launches of `steps` steps from the handle's current state, as lbm_vans_step
 // issues them without diagnostics (up to max_pass steps per launch), on h->stream;
@@ -3552,18 +3783,15 @@ constexpr int GRAPH_STEPS = 32;
 int plain_steps(lbm_vans_handle *h, int64_t steps)
 {
     for (int64_t k = 0; k < steps;) {
-        const int m = static_cast<int>(std::min<int64_t>(max_pass(h), steps - k));
-        const int rc = m >= 2 ? launch_multi(h, h->buf[h->cur], h->buf[1 - h->cur], m)
-                              : launch_sweep(h, false);
+        const int m = next_pass(h, steps - k);
+        const int rc = launch_pass(h, m);
         if (rc) return rc;
-        h->cur = 1 - h->cur;
-        h->n += m;
         k += m;
     }
     return LBM_VANS_OK;
 }
 
-// Capture GRAPH_STEPS steps from the current state slot (with the open-end rules of
+// Capture graph_steps steps from the current state slot (with the open-end rules of
 // a state n >= 1) into graph[h->cur]; the handle's state and count are unchanged.
 int capture_steps(lbm_vans_handle *h)
 {
@@ -3574,7 +3802,7 @@ int capture_steps(lbm_vans_handle *h)
     h->stream = h->cap;
     hipGraph_t graph = nullptr;
     hipError_t e = hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal);
-    int rc = e == hipSuccess ? plain_steps(h, GRAPH_STEPS) : LBM_VANS_OK;
+    int rc = e == hipSuccess ? plain_steps(h, graph_steps(h)) : LBM_VANS_OK;
     hipError_t e2 = e == hipSuccess ? hipStreamEndCapture(h->cap, &graph) : e;
     h->stream = st;
     h->cur = cur;
@@ -3605,43 +3833,39 @@ int lbm_vans_step(lbm_vans_handle *h, int64_t nsteps)
     // small lattices without diagnostics: whole chunks of steps as graph replays (the
     // same launches, without a host launch per step); the rest one launch at a time
     if (h->use_graphs && h->p.diag_every == 0) {
-        while (nsteps >= GRAPH_STEPS && res_on(&h->p, h->n)) {
+        const int steps = graph_steps(h);
+        while (nsteps >= steps && res_on(&h->p, h->n)) {
             if (!h->graph[h->cur]) {
                 const int rc = capture_steps(h);
                 if (rc) return rc;
             }
             HIP_TRY(hipGraphLaunch(h->graph[h->cur], h->stream));
-            const int64_t launches = (GRAPH_STEPS + max_pass(h) - 1) / max_pass(h);
-            if (launches & 1) h->cur = 1 - h->cur;
-            h->n += GRAPH_STEPS;
-            nsteps -= GRAPH_STEPS;
+            h->n += steps;
+            nsteps -= steps;
         }
     }
-    for (int64_t k = 0; k < nsteps; k++) {
-        bool diag = h->p.diag_every > 0 && h->n % h->p.diag_every == 0;
-        // up to three steps in one pass when they remain in this call and none
-        // records diagnostics
-        const int m = h->p.diag_every == 0
-                          ? static_cast<int>(std::min<int64_t>(max_pass(h), nsteps - k))
-                          : 1;
-        if (m >= 2) {
-            int rc = launch_multi(h, h->buf[h->cur], h->buf[1 - h->cur], m);
+    const int every = h->p.diag_every;
+    while (nsteps > 0) {
+        const bool diag = every > 0 && h->n % every == 0;
+        if (!diag) {
+            // as many steps as one launch takes, up to the next state to be recorded
+            const int64_t left = every > 0 ? std::min<int64_t>(nsteps, every - h->n % every)
+                                           : nsteps;
+            const int m = next_pass(h, left);
+            const int rc = launch_pass(h, m);
             if (rc) return rc;
-            h->cur = 1 - h->cur;
-            h->n += m;
-            k += m - 1;
+            nsteps -= m;
             continue;
         }
-        int rc = launch_sweep(h, diag);
+        int rc = launch_sweep(h, true);
         if (rc) return rc;
-        if (diag) {
-            double *slot = h->ring + (h->nrec % LBM_VANS_DIAG_RING) * NRED;
-            rc = launch_finalize(h, slot, h->gs.ntiles, true, static_cast<double>(h->n));
-            if (rc) return rc;
-            h->nrec++;
-        }
+        double *slot = h->ring + (h->nrec % LBM_VANS_DIAG_RING) * NRED;
+        rc = launch_finalize(h, slot, h->gs.ntiles, true, static_cast<double>(h->n));
+        if (rc) return rc;
+        h->nrec++;
         h->cur = 1 - h->cur;
         h->n++;
+        nsteps--;
     }
     return LBM_VANS_OK;
 }
@@ -3871,23 +4095,12 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
         for (int64_t s0 = 0; s0 < nsteps || s0 == 0; s0 += K) {
             HIP_TRY(hipMemcpyAsync(ckpt(s0 / K), h->buf[h->cur], G.pop, hipMemcpyDeviceToDevice,
                                    h->stream));
-            // only the checkpoints are kept, so the steps in between may go up to
-            // three per pass
-            for (int64_t k = 0; k < K && s0 + k < nsteps; k++) {
-                const int m = static_cast<int>(
-                    std::min<int64_t>({(int64_t)max_pass(h), K - k, nsteps - s0 - k}));
-                if (m >= 2) {
-                    r = launch_multi(h, h->buf[h->cur], h->buf[1 - h->cur], m);
-                    if (r) return r;
-                    h->cur = 1 - h->cur;
-                    h->n += m;
-                    k += m - 1;
-                    continue;
-                }
-                r = launch_sweep(h, false);
+            // only the checkpoints are kept: several steps per launch in between
+            for (int64_t k = 0; k < K && s0 + k < nsteps;) {
+                const int m = next_pass(h, std::min<int64_t>(K - k, nsteps - s0 - k));
+                r = launch_pass(h, m);
                 if (r) return r;
-                h->cur = 1 - h->cur;
-                h->n++;
+                k += m;
             }
             if (nsteps == 0) break;
         }
@@ -3939,10 +4152,17 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
         auto recompute = [&](int64_t c) -> int {
             const int64_t s0 = c * K, s1 = std::min<int64_t>(s0 + K, nsteps);
             const int64_t set = two ? c % 2 : 0;
-            for (int64_t j = 1; j < s1 - s0; j++) {
+            for (int64_t j = 1; j < s1 - s0;) {
                 const void *src = j == 1 ? (const void *)ckpt(c) : (const void *)seg(set, j - 1);
-                int rr = launch_sweep_ptrs(h, src, seg(set, j), s0 + j - 1, false, rs);
+                int m = 1, rr;
+                if (h->tile_ns) {              // every state of a launch is kept
+                    m = static_cast<int>(std::min<int64_t>(h->tile_ns, s1 - s0 - j));
+                    rr = launch_tile(h, src, seg(set, j), s0 + j - 1, m, G.pop, rs);
+                } else {
+                    rr = launch_sweep_ptrs(h, src, seg(set, j), s0 + j - 1, false, rs);
+                }
                 if (rr) return rr;
+                j += m;
             }
             if (two) HIP_TRY(hipEventRecord(h->ev_rec[set], rs));
             return LBM_VANS_OK;
