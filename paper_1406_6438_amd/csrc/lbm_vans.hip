@@ -120,7 +120,7 @@ int scratch_address(void **out)
 #ifndef LBM_VANS_ROWS
 #define LBM_VANS_ROWS 1
 #endif
-// rows each wave of the reverse step walks (k_adjoint_rows)
+// rows each wave of the row-walking reverse step walks (k_adjoint_rows)
 #ifndef LBM_VANS_ADJ_ROWS
 #define LBM_VANS_ADJ_ROWS 4
 #endif
@@ -385,15 +385,15 @@ __device__ __forceinline__ EpsTerms<R> eps_terms(R eps, R gex, R gey, const Phys
 }
 
 template <typename R, bool FUSED = false>
-__device__ __forceinline__ NodeFwd<R> node_forward_q(const R d[9], const EpsTerms<R> &q,
+__device__ __forceinline__ NodeFwd<R> node_forward_m(R dS, R mx, R my, const EpsTerms<R> &q,
                                                      const Phys<R> &ph)
 {
     NodeFwd<R> F;
     Node<R> &N = F.N;
-    N.dS = ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7])) + d[8];
+    N.dS = dS;
     N.S = FUSED ? fma_(q.e, ph.rho0, N.dS) : q.e * ph.rho0 + N.dS;
-    N.mx = (d[1] - d[3]) + (d[5] - d[6]) + (d[8] - d[7]);
-    N.my = (d[2] - d[4]) + (d[5] + d[6]) - (d[7] + d[8]);
+    N.mx = mx;
+    N.my = my;
     F.ie = q.ie;
     N.rho = N.S * F.ie;
     const R third = R(1) / R(3);
@@ -415,11 +415,29 @@ __device__ __forceinline__ NodeFwd<R> node_forward_q(const R d[9], const EpsTerm
     return F;
 }
 
+// Sum, and first moments, of nine deviations.
 template <typename R>
+__device__ __forceinline__ void sums_of(const R d[9], R &dS, R &mx, R &my)
+{
+    dS = ((d[0] + d[1]) + (d[2] + d[3])) + ((d[4] + d[5]) + (d[6] + d[7])) + d[8];
+    mx = (d[1] - d[3]) + (d[5] - d[6]) + (d[8] - d[7]);
+    my = (d[2] - d[4]) + (d[5] + d[6]) - (d[7] + d[8]);
+}
+
+template <typename R, bool FUSED = false>
+__device__ __forceinline__ NodeFwd<R> node_forward_q(const R d[9], const EpsTerms<R> &q,
+                                                     const Phys<R> &ph)
+{
+    R dS, mx, my;
+    sums_of<R>(d, dS, mx, my);
+    return node_forward_m<R, FUSED>(dS, mx, my, q, ph);
+}
+
+template <typename R, bool FUSED = false>
 __device__ __forceinline__ NodeFwd<R> node_forward(const R d[9], R eps, R gex, R gey,
                                                    const Phys<R> &ph)
 {
-    return node_forward_q<R>(d, eps_terms<R>(eps, gex, gey, ph), ph);
+    return node_forward_q<R, FUSED>(d, eps_terms<R>(eps, gex, gey, ph), ph);
 }
 
 template <typename R>
@@ -697,7 +715,7 @@ __device__ __forceinline__ void unshift_incoming(R d[9], const PorNb<R> &P, R rh
 // reservoir equilibria when the node is the first / last of an open x axis and
 // reservoirs are active (a y-wall wins at the corners), and the momentum a
 // sliding y-wall adds to the diagonals it returns.
-template <typename R>
+template <typename R, bool FUSED = false>
 __device__ __forceinline__ void boundary_inflow(R d[9], R e0, bool open_l, bool open_r,
                                                 bool wym, bool wyp, const Phys<R> &ph)
 {
@@ -713,12 +731,12 @@ __device__ __forceinline__ void boundary_inflow(R d[9], R e0, bool open_l, bool 
         if (!wyp) d[7] = e0 * ph.rout[7];
     }
     if (wym) {
-        d[5] += e0 * ph.wb;
-        d[6] -= e0 * ph.wb;
+        d[5] = FUSED ? fma_(e0, ph.wb, d[5]) : d[5] + e0 * ph.wb;
+        d[6] = FUSED ? fma_(-e0, ph.wb, d[6]) : d[6] - e0 * ph.wb;
     }
     if (wyp) {
-        d[8] += e0 * ph.wt;
-        d[7] -= e0 * ph.wt;
+        d[8] = FUSED ? fma_(e0, ph.wt, d[8]) : d[8] + e0 * ph.wt;
+        d[7] = FUSED ? fma_(-e0, ph.wt, d[7]) : d[7] - e0 * ph.wt;
     }
 }
 
@@ -768,7 +786,7 @@ __device__ __forceinline__ void update_node_q(R d[9], const PorNb<R> &P, const E
                                               bool wym, bool wyp, bool open_l, bool open_r,
                                               const Phys<R> &ph, double *acc, bool count)
 {
-    boundary_inflow<R>(d, P.e0, open_l, open_r, wym, wyp, ph);
+    boundary_inflow<R, FUSED>(d, P.e0, open_l, open_r, wym, wyp, ph);
     unshift_incoming<R, IN_FULL, FUSED>(d, P, ph.rho0);
     Node<R> N = node_forward_q<R, FUSED>(d, q, ph).N;
     if constexpr (DIAG) {
@@ -2253,47 +2271,40 @@ __device__ __forceinline__ void drag_derivs(const Phys<R> &ph, R eps, R inv_eps,
     db = -ph.cb + R(3) * ph.kb * eps * eps;
 }
 
-// Reverse of one node.  d: the node's incoming deviations (as update_node
-// sees them before the collision); mu: adjoints of its 9 post-collision
+// Reverse of one node.  F: the node's forward quantities (node_forward of its incoming
+// deviations); mu: adjoints of its 9 post-collision
 // values; S_bar0, ux_bar0, uy_bar0: adjoints of eps rho and u (the objective).
 // Returns the adjoints of the 9 incoming plain populations in nu and adds the
 // direct porosity and porosity-gradient adjoints to eb, gxb, gyb.
 template <typename R>
-__device__ __forceinline__ void node_vjp(const R d[9], R e0, R gex, R gey, const Phys<R> &ph,
-                                         const R mu[9], R S_bar0, R ux_bar0, R uy_bar0,
-                                         R nu[9], R &eb, R &gxb, R &gyb)
+__device__ __forceinline__ void node_vjp(const NodeFwd<R> &F, R e0, R gex, R gey,
+                                         const Phys<R> &ph, const R mu[9], R S_bar0, R ux_bar0,
+                                         R uy_bar0, R nu[9], R &eb, R &gxb, R &gyb)
 {
-    const NodeFwd<R> F = node_forward<R>(d, e0, gex, gey, ph);
     const Node<R> &N = F.N;
     const R om = ph.omega, P = ph.pre, S = N.S, ux = N.ux, uy = N.uy;
-    const R uu = ux * ux + uy * uy;
-    R S_bar = S_bar0, ux_bar = ux_bar0, uy_bar = uy_bar0;
-    R Tx_bar = R(0), Ty_bar = R(0), uu_bar = R(0), uT_bar = R(0);
     // out_i = (1 - omega) f_i + omega feq_i + src_i,
     // feq_i = w_i S (1 + A_i + A_i^2/2 - 3/2 u.u), src_i = P w_i (B_i (1 + A_i) - 3 u.T),
-    // A_i = 3 e_i.u, B_i = 3 e_i.T
-#pragma unroll
-    for (int i = 0; i < 9; i++) {
-        const R cx = R(CX[i]), cy = R(CY[i]);
-        const R w = i == 0 ? R(4) / R(9) : (i < 5 ? R(1) / R(9) : R(1) / R(36));
-        const R Ai = R(3) * (cx * ux + cy * uy);
-        const R Bi = R(3) * (cx * N.Tx + cy * N.Ty);
-        const R m = mu[i];
-        nu[i] = (R(1) - om) * m;
-        S_bar += om * m * w * (R(1) + Ai + R(0.5) * Ai * Ai - R(1.5) * uu);
-        const R A_bar = om * m * w * S * (R(1) + Ai) + m * P * w * Bi;
-        const R B_bar = m * P * w * (R(1) + Ai);
-        uu_bar -= R(1.5) * om * S * m * w;
-        uT_bar -= R(3) * P * m * w;
-        ux_bar += R(3) * cx * A_bar;
-        uy_bar += R(3) * cy * A_bar;
-        Tx_bar += R(3) * cx * B_bar;
-        Ty_bar += R(3) * cy * B_bar;
-    }
-    ux_bar += R(2) * ux * uu_bar + N.Tx * uT_bar;
-    uy_bar += R(2) * uy * uu_bar + N.Ty * uT_bar;
-    Tx_bar += ux * uT_bar;
-    Ty_bar += uy * uT_bar;
+    // A_i = 3 e_i.u, B_i = 3 e_i.T: at most quadratic in e_i, so the nine adjoints enter
+    // through the moments of m_i = w_i mu_i up to second order, M0 = sum m, M = sum e m and
+    // M2 = sum e e m.  With N2 = 3 M2 - M0 and K = M + N2 u:
+    //   S_bar = omega (M0 + 3/2 u.(M + K)),  T_bar = 3 P K,
+    //   u_bar = 3 omega S K + 3 P N2 T.
+    const R w = R(1) / R(36);
+    const R a13 = mu[1] + mu[3], b13 = mu[1] - mu[3], a24 = mu[2] + mu[4], b24 = mu[2] - mu[4];
+    const R a57 = mu[5] + mu[7], b57 = mu[5] - mu[7], a68 = mu[6] + mu[8], b68 = mu[6] - mu[8];
+    const R ad = a57 + a68;
+    const R M0 = w * (R(16) * mu[0] + (R(4) * (a13 + a24) + ad));
+    const R Mx = w * (R(4) * b13 + (b57 - b68)), My = w * (R(4) * b24 + (b57 + b68));
+    const R w3 = R(3) * w;
+    const R Nxx = w3 * (R(4) * a13 + ad) - M0, Nyy = w3 * (R(4) * a24 + ad) - M0;
+    const R Nxy = w3 * (a57 - a68);
+    const R Kx = Mx + (Nxx * ux + Nxy * uy), Ky = My + (Nxy * ux + Nyy * uy);
+    const R oS3 = R(3) * om * S, P3 = R(3) * P;
+    R S_bar = S_bar0 + om * (M0 + R(1.5) * (ux * (Mx + Kx) + uy * (My + Ky)));
+    const R Tx_bar = P3 * Kx, Ty_bar = P3 * Ky;
+    R ux_bar = ux_bar0 + (oS3 * Kx + P3 * (Nxx * N.Tx + Nxy * N.Ty));
+    R uy_bar = uy_bar0 + (oS3 * Ky + P3 * (Nxy * N.Tx + Nyy * N.Ty));
     // T = Q + G - drag u, drag = a + b |u|
     R Qx_bar = Tx_bar, Qy_bar = Ty_bar;
     const R drag_bar = -(Tx_bar * ux + Ty_bar * uy);
@@ -2329,8 +2340,17 @@ __device__ __forceinline__ void node_vjp(const R d[9], R e0, R gex, R gey, const
     drag_derivs(ph, e0, F.ie, da, db);
     eb += -rho_bar * S * F.ie * F.ie + a_bar * da + b_bar * db;
     // S = sum f, m = sum e f
-#pragma unroll
-    for (int i = 0; i < 9; i++) nu[i] += S_bar + R(CX[i]) * Vx_bar + R(CY[i]) * Vy_bar;
+    const R omc = R(1) - om;
+    const R xp = S_bar + Vx_bar, xm = S_bar - Vx_bar;
+    nu[0] = omc * mu[0] + S_bar;
+    nu[1] = omc * mu[1] + xp;
+    nu[2] = omc * mu[2] + (S_bar + Vy_bar);
+    nu[3] = omc * mu[3] + xm;
+    nu[4] = omc * mu[4] + (S_bar - Vy_bar);
+    nu[5] = omc * mu[5] + (xp + Vy_bar);
+    nu[6] = omc * mu[6] + (xm + Vy_bar);
+    nu[7] = omc * mu[7] + (xm - Vy_bar);
+    nu[8] = omc * mu[8] + (xp - Vy_bar);
 }
 
 // The reverse of one node at one step.  d: the node's incoming deviations of the
@@ -2368,7 +2388,7 @@ __device__ __forceinline__ void adjoint_node(const R d[9], const PorNb<R> &P, co
                 if (!n.wyp) { S_bar0 += mu[6] * (w2 + ph.rin[8]); mu[6] = R(0); }
             }
             if (orr) {
-                const Node<R> N = node_moments<R>(d, P.e0, P.gex, P.gey, ph);
+                const Node<R> N = node_forward<R, true>(d, P.e0, P.gex, P.gey, ph).N;
                 const R uu = N.ux * N.ux + N.uy * N.uy;
                 const R er = P.e0 * ph.rho_out;
                 // plain value w (eps rho_out) P(u): d/d eps = w rho_out P(u),
@@ -2390,7 +2410,8 @@ __device__ __forceinline__ void adjoint_node(const R d[9], const PorNb<R> &P, co
     e_b = e_end;
     gx_b = R(0);
     gy_b = R(0);
-    node_vjp<R>(d, P.e0, P.gex, P.gey, ph, mu, S_bar0, ux_bar0, uy_bar0, nu, e_b, gx_b, gy_b);
+    node_vjp<R>(node_forward<R, true>(d, P.e0, P.gex, P.gey, ph), P.e0, P.gex, P.gey, ph, mu,
+                S_bar0, ux_bar0, uy_bar0, nu, e_b, gx_b, gy_b);
     // reservoir links: the incoming value is eps0 * (rin_i + w_i rho0)
 #pragma unroll
     for (int i = 0; i < 9; i++) res[i] = false;
@@ -2528,7 +2549,8 @@ __global__ __launch_bounds__(NTHREADS) void k_adjoint_seed(const S *__restrict__
 }
 
 // One reverse step (no seed) with each wave walking K consecutive rows of a
-// 64-column strip, top to bottom.  The loads of row r + 1 (its adjoints, its
+// 64-column strip, top to bottom: planes of 2^31 bytes or more in FP64, past the 32-bit
+// offsets of the reverse tiles.  The loads of row r + 1 (its adjoints, its
 // gather, its accumulators and the porosity row above it) are issued before the
 // arithmetic of row r, so that a row's FP64 arithmetic runs under the memory
 // latency of the next one instead of after it.  A node's porosity window is
@@ -2640,6 +2662,230 @@ __global__ __launch_bounds__(NTHREADS) void k_adjoint_rows(
     const int strip = wid % nstrips, chunk = wid / nstrips;
     if (chunk >= nchunks) return;              // whole waves only; no barrier below
     adjoint_rows_wave<S, R, K>(fin, lam_next, lam, eps, g, ph, eb, gxb, gyb, strip, chunk);
+}
+
+// ---- reverse steps on a tile held by one workgroup ----------------------------------
+// One node per thread: a workgroup takes a tile of TW x TH nodes back through ns <= h + 1
+// states (st.f[0] the latest) and owns its inner nodes, those at least h from the tile's
+// edge.  The first reverse step reads the adjoints of the nodes' outgoing values from
+// memory (each node's own slots); between the steps a node's incoming adjoints go to the
+// nodes that sent the values, through LDS (two buffers in turn, one barrier a step; in
+// the adjoints' stored type, so that the result does not depend on how steps are grouped
+// into launches); the last step pushes the owned nodes' to memory.  The porosity
+// sensitivities of the owned nodes are added step by step to sums read once and written
+// once per launch.  The next state's loads are issued before a step's arithmetic.
+// Bound by its registers: FP64 arithmetic with the state of the next step in flight takes
+// 2 waves per SIMD (3 or 4 spill and take longer), so neither the FP64 units nor the memory
+// is kept busy; the discarded rings add 78% of arithmetic at three steps, the bytes a step
+// has to move fall from 160 to 77 (FP32: its state 36, a third of the rest).  One launch per step, four rows of a column per
+// lane, before / now, us per whole gradient: 1024 x 512 channel of 200 steps 7670 / 6550,
+// 256 x 128 of 200 3990 / 2090, 512 x 300 FP64 of 100 2870 / 2310, six channels of
+// 256 to 1024 columns, 90 steps, 6900 / 5940.  Not as fast at 1024 x 512: one step per launch on 64 x 4 nodes
+// (7450 to 7550), two on 32 x 16 (7020 to 7450).
+constexpr int REV_W = 16, REV_H = 16;   // nodes of a tile
+constexpr int REV_STEPS = 3;            // most steps of a launch
+constexpr int REV_OW = REV_W - 2 * (REV_STEPS - 1), REV_OH = REV_H - 2 * (REV_STEPS - 1);
+
+template <typename S>
+struct RevStates {
+    const S *f[REV_STEPS];   // the states of the launch's steps, latest first
+    int res;                 // bit s: the open-end rules apply to step s
+};
+
+template <typename S, int BX, bool WY>
+__device__ __forceinline__ void reverse_tile(const RevStates<S> &st,
+                                             const AdjT<S> *__restrict__ lam_next,
+                                             AdjT<S> *__restrict__ lam,
+                                             const AdjT<S> *__restrict__ eps, const Geo &g,
+                                             const Phys<double> &ph, double *__restrict__ eb,
+                                             double *__restrict__ gxb, double *__restrict__ gyb,
+                                             int ns, int bx, int by,
+                                             AdjT<S> (*buf)[8][REV_W * REV_H])
+{
+    using A = AdjT<S>;
+    using R = double;
+    constexpr bool WX = BX != 0;
+    constexpr int TW = REV_W, TH = REV_H, h = REV_STEPS - 1;
+    const int tid = threadIdx.x, tx = tid % TW, ty = tid / TW;
+    const int xu = bx * REV_OW - h + tx, yu = by * REV_OH - h + ty;
+    auto inside = [](int v, int L, bool wall, int T) {
+        if (wall) return min(max(v, 0), L - 1);
+        if (L < T) v %= L;                     // uniform
+        return v < 0 ? v + L : (v >= L ? v - L : v);
+    };
+    const int x = inside(xu, g.Lx, WX, TW), y = inside(yu, g.Ly, WY, TH);
+    const bool own = tx >= h && tx < TW - h && ty >= h && ty < TH - h && xu < g.Lx && yu < g.Ly;
+    Nbr n;
+    n.wxm = WX && x == 0;
+    n.wxp = WX && x == g.Lx - 1;
+    n.wym = WY && y == 0;
+    n.wyp = WY && y == g.Ly - 1;
+    const bool edge = (WX || WY) && (n.wxm || n.wxp || n.wym || n.wyp);
+    // element offsets within a plane (the host keeps a plane's bytes below 2^31): the slot
+    // each direction is pulled from, the node itself behind an end
+    const unsigned lx = static_cast<unsigned>(g.Lx), pitch = static_cast<unsigned>(g.pitch);
+    const unsigned c0 = x, cm = x == 0 ? (WX ? 0u : lx - 1) : x - 1u;
+    const unsigned cp = x == g.Lx - 1 ? (WX ? lx - 1 : 0u) : x + 1u;
+    const unsigned q0 = y * pitch, qm = (y == 0 ? (WY ? 0u : g.Ly - 1u) : y - 1u) * pitch;
+    const unsigned qp = (y == g.Ly - 1 ? (WY ? g.Ly - 1u : 0u) : y + 1u) * pitch;
+    const unsigned c = q0 + c0;
+    const unsigned slot[9] = {c, q0 + cm, qm + c0, q0 + cp, qp + c0,
+                              qm + cm, qm + cp, qp + cp, qp + cm};
+    auto at = [](auto *base, unsigned k) {     // a uniform base, a 32-bit byte offset
+        using T = std::remove_pointer_t<decltype(base)>;
+        using C = std::conditional_t<std::is_const_v<T>, const char, char>;
+        return to_global(reinterpret_cast<T *>(reinterpret_cast<C *>(base) +
+                                               k * static_cast<unsigned>(sizeof(T))));
+    };
+    // behind an end: the node's own opposite value
+    auto bounce = [&](auto *f, const auto *o) {
+        f[1] = n.wxm ? o[3] : f[1];
+        f[2] = n.wym ? o[4] : f[2];
+        f[3] = n.wxp ? o[1] : f[3];
+        f[4] = n.wyp ? o[2] : f[4];
+        f[5] = (n.wxm || n.wym) ? o[7] : f[5];
+        f[6] = (n.wxp || n.wym) ? o[8] : f[6];
+        f[7] = (n.wxp || n.wyp) ? o[5] : f[7];
+        f[8] = (n.wxm || n.wyp) ? o[6] : f[8];
+    };
+    S v[9], w[9];                              // this step's state, the next one's
+    auto fetch = [&](S (&f)[9], const S *state) {
+#pragma unroll
+        for (int i = 0; i < 9; i++) f[i] = *at(state + i * g.plane, slot[i]);
+        if (edge) {
+            S o[9];
+#pragma unroll
+            for (int i = 1; i < 9; i++) o[i] = *at(state + i * g.plane, c);
+            bounce(f, o);
+        }
+    };
+    A mu[9];
+#pragma unroll
+    for (int i = 0; i < 9; i++) mu[i] = *at(lam_next + i * g.plane, c);
+    fetch(v, st.f[0]);
+    const A e[3][3] = {{*at(eps, qm + cm), *at(eps, qm + c0), *at(eps, qm + cp)},
+                       {*at(eps, q0 + cm), *at(eps, q0 + c0), *at(eps, q0 + cp)},
+                       {*at(eps, qp + cm), *at(eps, qp + c0), *at(eps, qp + cp)}};
+    double se = 0.0, sx = 0.0, sy = 0.0;
+    if (own) {
+        se = *at(eb, c);
+        sx = *at(gxb, c);
+        sy = *at(gyb, c);
+    }
+    const R t[3][3] = {{R(e[0][0]), R(e[0][1]), R(e[0][2])},
+                       {R(e[1][0]), R(e[1][1]), R(e[1][2])},
+                       {R(e[2][0]), R(e[2][1]), R(e[2][2])}};
+    const PorNb<R> P = porosity_nb<R, 3>(t, 1, 1, n.wxm, n.wxp, n.wym, n.wyp);
+    const EpsTerms<R> q = eps_terms<R>(P.e0, P.gex, P.gey, ph);
+    // (finished here: fused into a step's sums they would round differently in the steps
+    // where the compiler keeps them and where it forms them anew)
+    R lgx = P.gex * (ph.rho0 / R(6)), lgy = P.gey * (ph.rho0 / R(6));
+    R lap = ph.rho0 * (((P.D[1] + P.D[2]) + (P.D[3] + P.D[4])) / R(18) +
+                       ((P.D[5] + P.D[6]) + (P.D[7] + P.D[8])) / R(72));
+    asm volatile("" : "+v"(lgx), "+v"(lgy), "+v"(lap));
+    // neighbours in the tile: the node a population is sent to
+    const int lm = max(tx - 1, 0), lp = min(tx + 1, TW - 1);
+    const int r0 = ty * TW, rm = max(ty - 1, 0) * TW, rp = min(ty + 1, TH - 1) * TW;
+    // one copy of the step for every s: the same roundings in each
+#pragma clang loop unroll(disable)
+    for (int s = 0;; s++) {
+        const bool last = s == ns - 1;         // uniform
+        if (!last) {
+            const S *next = st.f[1];
+#pragma unroll
+            for (int k = 2; k < REV_STEPS; k++) next = s + 1 == k ? st.f[k] : next;
+            fetch(w, next);
+        }
+        R m[9], nu[9], e_b = 0.0, gx_b = 0.0, gy_b = 0.0;
+        bool res[9] = {};
+#pragma unroll
+        for (int i = 0; i < 9; i++) m[i] = static_cast<R>(mu[i]);
+        R d[9];
+#pragma unroll
+        for (int i = 0; i < 9; i++) d[i] = decode_pop<S, R>(v[i], ph.inv_scale);
+        if constexpr (!WX && !WY) {
+            // no ends: the link shifts enter the sums through the porosity's Laplacian
+            // and gradient alone
+            R dS, mx, my;
+            sums_of<R>(d, dS, mx, my);
+            const NodeFwd<R> F = node_forward_m<R, true>(dS + lap, mx - lgx, my - lgy, q, ph);
+            node_vjp<R>(F, P.e0, P.gex, P.gey, ph, m, 0.0, 0.0, 0.0, nu, e_b, gx_b, gy_b);
+        } else {
+            const bool ores = BX == 2 && (st.res >> s & 1);
+            const bool ol = ores && n.wxm, orr = ores && n.wxp;
+            boundary_inflow<R, true>(d, P.e0, ol, orr, n.wym, n.wyp, ph);
+            unshift_incoming<R, false, true>(d, P, ph.rho0);
+            adjoint_node<R, false>(d, P, n, ol, orr, WX && n.wxp, ph, m, nu, res, e_b, gx_b, gy_b,
+                                   nullptr);
+        }
+        se += e_b;
+        sx += gx_b;
+        sy += gy_b;
+        A o[9];
+#pragma unroll
+        for (int i = 0; i < 9; i++) o[i] = res[i] ? A(0) : static_cast<A>(nu[i]);
+        if (last) {
+            if (own) {
+                // to the slot each value was pulled from (behind an end the node's own
+                // opposite one)
+                const bool b[9] = {false, n.wxm, n.wym, n.wxp, n.wyp, n.wxm || n.wym,
+                                   n.wxp || n.wym, n.wxp || n.wyp, n.wxm || n.wyp};
+                const int opp[9] = {0, 3, 4, 1, 2, 7, 8, 5, 6};
+#pragma unroll
+                for (int i = 0; i < 9; i++) {
+                    if (!(WX || WY) || !b[i]) *at(lam + i * g.plane, slot[i]) = o[i];
+                    else *at(lam + opp[i] * g.plane, c) = o[i];
+                }
+                *at(eb, c) = se;
+                *at(gxb, c) = sx;
+                *at(gyb, c) = sy;
+            }
+            return;                            // uniform over the workgroup
+        }
+        A(*b)[TW * TH] = buf[s & 1];
+#pragma unroll
+        for (int i = 1; i < 9; i++) b[i - 1][tid] = o[i];
+        __syncthreads();
+        mu[0] = o[0];
+        mu[1] = n.wxp ? o[3] : b[0][r0 + lp];
+        mu[2] = n.wyp ? o[4] : b[1][rp + tx];
+        mu[3] = n.wxm ? o[1] : b[2][r0 + lm];
+        mu[4] = n.wym ? o[2] : b[3][rm + tx];
+        mu[5] = (n.wxp || n.wyp) ? o[7] : b[4][rp + lp];
+        mu[6] = (n.wxm || n.wyp) ? o[8] : b[5][rp + lm];
+        mu[7] = (n.wxm || n.wym) ? o[5] : b[6][rm + lm];
+        mu[8] = (n.wxp || n.wym) ? o[6] : b[7][rm + lp];
+#pragma unroll
+        for (int i = 0; i < 9; i++) v[i] = w[i];
+    }
+}
+
+// Whether the tile takes the step built without x-end and y-wall rules: no node of it lies
+// at an end or beyond (uniform over the workgroup).  Not with FP64 storage, whose gradient
+// is the same to the bit for any checkpoint interval: the two forms round differently, and
+// a node in the ring of one tile may be owned by a tile of the other kind.
+template <typename S, int BX, bool WY>
+__device__ __forceinline__ bool tile_clear(int bx, int by, const Geo &g)
+{
+    if (std::is_same_v<S, double> && (BX != 0 || WY)) return false;
+    const int h = REV_STEPS - 1, x0 = bx * REV_OW - h, y0 = by * REV_OH - h;
+    return (BX == 0 || (x0 >= 1 && x0 + REV_W <= g.Lx - 1)) &&
+           (!WY || (y0 >= 1 && y0 + REV_H <= g.Ly - 1));
+}
+
+template <typename S, int BX, bool WY>
+__global__ __launch_bounds__(REV_W *REV_H) __attribute__((amdgpu_waves_per_eu(2)))
+void k_reverse_tile(RevStates<S> st, const AdjT<S> *__restrict__ lam_next,
+                    AdjT<S> *__restrict__ lam, const AdjT<S> *__restrict__ eps, Geo g,
+                    Phys<double> ph, double *__restrict__ eb, double *__restrict__ gxb,
+                    double *__restrict__ gyb, int ns, int ntx)
+{
+    __shared__ AdjT<S> buf[2][8][REV_W * REV_H];
+    const int t = xcd_tile(blockIdx.x, gridDim.x), bx = t % ntx, by = t / ntx;
+    if (tile_clear<S, BX, WY>(bx, by, g))
+        reverse_tile<S, 0, false>(st, lam_next, lam, eps, g, ph, eb, gxb, gyb, ns, bx, by, buf);
+    else
+        reverse_tile<S, BX, WY>(st, lam_next, lam, eps, g, ph, eb, gxb, gyb, ns, bx, by, buf);
 }
 
 // Initial state: f_i(r, 0) = w_i eps(r) rho0 (1 + 3 e_i.u0 + 9/2 (e_i.u0)^2 -
@@ -2780,6 +3026,7 @@ struct Member {
     int vec;                // nodes per lane of this member's sweep
     int tile0;              // first position in the sweep tile list of its width
     int tile0_adj;          // first position in the adjoint tile list
+    int tile0_rev, rev_tx;  // first position in the reverse tile list, tiles in x
     int tb_strips[3];       // strips of the two-, three- and four-step passes
     int tw0[4];             // first position in the wave lists of the two-step pass, of
                             // the three-step pass in short and in tall chunks, and of
@@ -2922,8 +3169,40 @@ __global__ __launch_bounds__(NTHREADS) void k_batch_adjoint_seed(
                                  acc_buf(d, 1), acc_buf(d, 2), d.part, T - d.tile0_adj);
 }
 
-// One reverse step (no seed) of every member, one wave per entry of the adjoint
-// tile list: a tile of TX columns and TY rows is the strip and chunk one wave of
+// Up to REV_STEPS reverse steps (no seed) of every member, one workgroup per entry of the
+// reverse tile list; slots: the states' slots, latest first.
+struct RevSlots {
+    int slot[REV_STEPS], res;
+};
+
+template <typename S, typename R, int BX, bool WY>
+__global__ __launch_bounds__(REV_W *REV_H) __attribute__((amdgpu_waves_per_eu(2)))
+void k_batch_reverse_tile(const Member<R> *__restrict__ M, const int *__restrict__ tmap,
+                          int ntiles, RevSlots slots, int ns, int a_next, int a)
+{
+    __shared__ AdjT<S> buf[2][8][REV_W * REV_H];
+    const int T = xcd_tile(blockIdx.x, ntiles);
+    const Member<R> &d = M[tmap[T]];
+    const Geo g = d.g;
+    const Phys<double> ph = d.pha;
+    RevStates<S> st;
+    st.res = slots.res;
+#pragma unroll
+    for (int k = 0; k < REV_STEPS; k++)
+        st.f[k] = reinterpret_cast<const S *>(state_slot(d, slots.slot[k]));
+    const AdjT<S> *ln = adj_buf<AdjT<S>>(d, a_next);
+    AdjT<S> *l = adj_buf<AdjT<S>>(d, a);
+    const AdjT<S> *eps = reinterpret_cast<const AdjT<S> *>(d.eps);
+    double *eb = acc_buf(d, 0), *gxb = acc_buf(d, 1), *gyb = acc_buf(d, 2);
+    const int t = T - d.tile0_rev, bx = t % d.rev_tx, by = t / d.rev_tx;
+    if (tile_clear<S, BX, WY>(bx, by, g))
+        reverse_tile<S, 0, false>(st, ln, l, eps, g, ph, eb, gxb, gyb, ns, bx, by, buf);
+    else
+        reverse_tile<S, BX, WY>(st, ln, l, eps, g, ph, eb, gxb, gyb, ns, bx, by, buf);
+}
+
+// One reverse step (no seed) of every member where a member's planes are too large for the
+// reverse tiles, one wave per entry of the adjoint tile list: a tile of TX columns and TY rows is the strip and chunk one wave of
 // the row-walking reverse step takes.
 template <typename S, typename R>
 __global__ __launch_bounds__(NTHREADS) void k_batch_adjoint_rows(const Member<R> *__restrict__ M,
@@ -4082,6 +4361,13 @@ GradLayout grad_layout(const lbm_vans_params *p, int64_t nsteps, int32_t ckpt_ev
     return G;
 }
 
+// Whether the reverse tiles' 32-bit byte offsets reach every node of a plane (FP64).
+bool reverse_fits(const Geo &g) { return g.plane * 8 < (1LL << 31); }
+
+// Reverse tiles of a lattice.
+int reverse_tiles_x(const Geo &g) { return (g.Lx + REV_OW - 1) / REV_OW; }
+int reverse_tiles(const Geo &g) { return reverse_tiles_x(g) * ((g.Ly + REV_OH - 1) / REV_OH); }
+
 int check_grad_args(const lbm_vans_params *p, int32_t objective, int64_t nsteps,
                     int32_t ckpt_every)
 {
@@ -4203,6 +4489,8 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
         const int adj_chunks = (g.Ly + ADJ_ROWS - 1) / ADJ_ROWS;
         const unsigned adj_blocks =
             static_cast<unsigned>(((long long)adj_strips * adj_chunks + NW - 1) / NW);
+        // where a plane's bytes do not fit the tiles' 32-bit offsets
+        const bool rev = reverse_fits(g);
         hipStream_t rs = two ? h->stream2 : h->stream;
         auto recompute = [&](int64_t c) -> int {
             const int64_t s0 = c * K, s1 = std::min<int64_t>(s0 + K, nsteps);
@@ -4244,9 +4532,31 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
                 if (r) return r;
             }
             if (two) HIP_TRY(hipStreamWaitEvent(h->stream, h->ev_rec[set], 0));
-            for (int64_t n = s1 - 1; n >= s0; n--) {
-                const void *state =
-                    n == s0 ? (const void *)ckpt(c) : (const void *)seg(set, n - s0);
+            auto state_of = [&](int64_t n) {
+                return n == s0 ? (const S *)ckpt(c) : (const S *)seg(set, n - s0);
+            };
+            for (int64_t n = s1 - 1; rev && n >= s0;) {
+                const int m = static_cast<int>(std::min<int64_t>(REV_STEPS, n - s0 + 1));
+                RevStates<S> st{};
+                for (int k = 0; k < m; k++) {
+                    st.f[k] = state_of(n - k);
+                    st.res |= (res_on(&h->p, n - k) ? 1 : 0) << k;
+                }
+                with_bxwy(g.open_x ? 2 : (g.wall_x ? 1 : 0), g.wall_y, [&](auto bxc, auto wyc) {
+                    hipLaunchKernelGGL((k_reverse_tile<S, decltype(bxc)::value,
+                                                       decltype(wyc)::value>),
+                                       dim3(reverse_tiles(g)), dim3(REV_W * REV_H), 0, h->stream,
+                                       st, (const AdjT<S> *)lam[a], (AdjT<S> *)lam[1 - a],
+                                       (const AdjT<S> *)h->eps, g, ph, eb, gxb, gyb, m,
+                                       reverse_tiles_x(g));
+                });
+                r = check_launch("k_reverse_tile");
+                if (r) return r;
+                a = 1 - a;
+                n -= m;
+            }
+            for (int64_t n = s1 - 1; !rev && n >= s0; n--) {
+                const void *state = state_of(n);
                 ph.reservoir = res_on(&h->p, n);
                 hipLaunchKernelGGL((k_adjoint_rows<S, RA, ADJ_ROWS>), dim3(adj_blocks),
                                    dim3(NTHREADS), 0, h->stream, (const S *)state,
@@ -4333,14 +4643,16 @@ struct lbm_vans_batch {
     lbm_vans_batch_config cfg{};
     size_t desc_bytes = 0;          // bytes of one device descriptor
     std::vector<char> desc;         // host image of the descriptors
-    std::vector<int> tmap, tmap_adj;  // tile lists of the sweep and of the adjoint
+    std::vector<int> tmap, tmap_adj, tmap_rev;  // tile lists of the sweep, the adjoint's seed
+                                                // and the reverse steps
     std::vector<int> wmap[4];         // wave lists of the two-step pass, of the three-step
                                       // pass in short and in tall chunks (FP32 only) and of
                                       // the four-step pass (FP32 only)
     void *d_desc = nullptr;
-    int *d_tmap = nullptr, *d_tmap_adj = nullptr,
+    int *d_tmap = nullptr, *d_tmap_adj = nullptr, *d_tmap_rev = nullptr,
         *d_wmap[4] = {nullptr, nullptr, nullptr, nullptr};
-    int ntiles = 0, ntiles_adj = 0, nwaves[4] = {0, 0, 0, 0};
+    int ntiles = 0, ntiles_adj = 0, ntiles_rev = 0, nwaves[4] = {0, 0, 0, 0};
+    bool rev_ok = true;             // every member fits the reverse tiles' addressing
     bool multi_ok = true;           // every member fits the multi-step passes' addressing
     bool multi4_ok = false;         // ... and the four-step pass (FP32, rows)
     long long tall_resident = 0;    // waves of the tall batched three-step kernel the chip holds
@@ -4350,10 +4662,12 @@ struct lbm_vans_batch {
 
 namespace {
 
-size_t batch_table_bytes(int storage, size_t nmembers, size_t ntiles_adj, const size_t *nwaves)
+size_t batch_table_bytes(int storage, size_t nmembers, size_t ntiles_adj, size_t ntiles_rev,
+                         const size_t *nwaves)
 {
     const size_t d = storage == LBM_F64 ? sizeof(Member<double>) : sizeof(Member<float>);
     return align256(nmembers * d) + 2 * align256(ntiles_adj * sizeof(int)) +
+           align256(ntiles_rev * sizeof(int)) +
            align256(nwaves[0] * sizeof(int)) + align256(nwaves[1] * sizeof(int)) +
            align256(nwaves[2] * sizeof(int)) + align256(nwaves[3] * sizeof(int));
 }
@@ -4397,6 +4711,7 @@ int batch_upload(lbm_vans_batch *b, int vec, char *gw, int64_t nsteps, int32_t c
     const size_t nm = b->m.size();
     b->tmap.clear();
     b->tmap_adj.clear();
+    b->tmap_rev.clear();
     for (auto &wm : b->wmap) wm.clear();
     int rc = with_types(b->storage, [&](auto *sp, auto *rp) -> int {
         using R = std::remove_pointer_t<decltype(rp)>;
@@ -4423,6 +4738,9 @@ int batch_upload(lbm_vans_batch *b, int vec, char *gw, int64_t nsteps, int32_t c
             d.tile0_adj = static_cast<int>(b->tmap_adj.size());
             b->tmap.insert(b->tmap.end(), d.gs.ntiles, static_cast<int>(k));
             b->tmap_adj.insert(b->tmap_adj.end(), d.g.ntiles, static_cast<int>(k));
+            d.tile0_rev = static_cast<int>(b->tmap_rev.size());
+            d.rev_tx = reverse_tiles_x(d.g);
+            b->tmap_rev.insert(b->tmap_rev.end(), reverse_tiles(d.g), static_cast<int>(k));
             for (int q = 0; q < 4; q++) {
                 const int ns = q == 0 ? 2 : (q < 3 ? 3 : 4);
                 const int cols = TX - 2 * (ns - 1);
@@ -4454,12 +4772,15 @@ int batch_upload(lbm_vans_batch *b, int vec, char *gw, int64_t nsteps, int32_t c
     if (rc) return rc;
     b->ntiles = static_cast<int>(b->tmap.size());
     b->ntiles_adj = static_cast<int>(b->tmap_adj.size());
+    b->ntiles_rev = static_cast<int>(b->tmap_rev.size());
     for (int q = 0; q < 4; q++) b->nwaves[q] = static_cast<int>(b->wmap[q].size());
     HIP_TRY(hipMemcpyAsync(b->d_desc, b->desc.data(), b->desc.size(), hipMemcpyHostToDevice,
                            b->stream));
     HIP_TRY(hipMemcpyAsync(b->d_tmap, b->tmap.data(), b->tmap.size() * sizeof(int),
                            hipMemcpyHostToDevice, b->stream));
     HIP_TRY(hipMemcpyAsync(b->d_tmap_adj, b->tmap_adj.data(), b->tmap_adj.size() * sizeof(int),
+                           hipMemcpyHostToDevice, b->stream));
+    HIP_TRY(hipMemcpyAsync(b->d_tmap_rev, b->tmap_rev.data(), b->tmap_rev.size() * sizeof(int),
                            hipMemcpyHostToDevice, b->stream));
     for (int q = 0; q < 4; q++)
         if (!b->wmap[q].empty())
@@ -4600,6 +4921,24 @@ int batch_adjoint(lbm_vans_batch *b, bool seed, int src, int a_next, int a, int 
     });
 }
 
+// m (1 .. REV_STEPS) reverse steps of every member in one launch, from the adjoints in
+// a_next to those in a.
+int batch_reverse(lbm_vans_batch *b, const RevSlots &slots, int m, int a_next, int a)
+{
+    return with_types(b->storage, [&](auto *sp, auto *rp) -> int {
+        using S = std::remove_pointer_t<decltype(sp)>;
+        using R = std::remove_pointer_t<decltype(rp)>;
+        with_bxwy(b->bx, b->wy, [&](auto bxc, auto wyc) {
+            hipLaunchKernelGGL((k_batch_reverse_tile<S, R, decltype(bxc)::value,
+                                                     decltype(wyc)::value>),
+                               dim3(b->ntiles_rev), dim3(REV_W * REV_H), 0, b->stream,
+                               static_cast<const Member<R> *>(b->d_desc),
+                               (const int *)b->d_tmap_rev, b->ntiles_rev, slots, m, a_next, a);
+        });
+        return check_launch("k_batch_reverse_tile");
+    });
+}
+
 // Capture cfg.graph_steps steps starting from slot s0 (all with the
 // reservoirs active, i.e. from a state n >= 1) into an executable graph.
 int batch_capture(lbm_vans_batch *b, int s0)
@@ -4680,13 +5019,14 @@ extern "C" {
 size_t lbm_vans_batch_work_bytes(lbm_vans_handle *const *members, int32_t nmembers)
 {
     if (!members || nmembers < 1) return 0;
-    size_t tiles = 0, waves[4] = {0, 0, 0, 0};
+    size_t tiles = 0, rtiles = 0, waves[4] = {0, 0, 0, 0};
     for (int32_t k = 0; k < nmembers; k++) {
         if (!members[k]) return 0;
         tiles += static_cast<size_t>(members[k]->g.ntiles);
+        rtiles += static_cast<size_t>(reverse_tiles(members[k]->g));
         for (int q = 0; q < 4; q++) waves[q] += batch_waves(&members[k]->p, q);
     }
-    return batch_table_bytes(members[0]->p.storage, nmembers, tiles, waves);
+    return batch_table_bytes(members[0]->p.storage, nmembers, tiles, rtiles, waves);
 }
 
 int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, void *work,
@@ -4698,7 +5038,7 @@ int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, voi
     if (!members || nmembers < 1) return fail(LBM_VANS_EINVAL, "no members");
     const lbm_vans_handle *h0 = members[0];
     if (!h0) return fail(LBM_VANS_EINVAL, "member 0 is NULL");
-    size_t tiles = 0, waves[4] = {0, 0, 0, 0};
+    size_t tiles = 0, rtiles = 0, waves[4] = {0, 0, 0, 0};
     for (int32_t k = 0; k < nmembers; k++) {
         const lbm_vans_handle *h = members[k];
         if (!h) return fail(LBM_VANS_EINVAL, "member %d is NULL", k);
@@ -4714,16 +5054,17 @@ int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, voi
             return fail(LBM_VANS_EINVAL, "member %d is at step %lld, member 0 at %lld", k,
                         (long long)h->n, (long long)h0->n);
         tiles += static_cast<size_t>(h->g.ntiles);
+        rtiles += static_cast<size_t>(reverse_tiles(h->g));
         for (int q = 0; q < 4; q++) waves[q] += batch_waves(&h->p, q);
     }
-    if (tiles > static_cast<size_t>(INT32_MAX))
-        return fail(LBM_VANS_EINVAL, "%zu tiles: too many for one launch", tiles);
+    if (std::max(tiles, rtiles) > static_cast<size_t>(INT32_MAX))
+        return fail(LBM_VANS_EINVAL, "%zu tiles: too many for one launch", std::max(tiles, rtiles));
     const size_t wmax = std::max({waves[0], waves[1], waves[2], waves[3]});
     if (wmax > static_cast<size_t>(INT32_MAX - NW))
         return fail(LBM_VANS_EINVAL, "%zu waves: too many for one launch", wmax);
     if (!work || reinterpret_cast<uintptr_t>(work) % 256)
         return fail(LBM_VANS_EINVAL, "work must be a 256-byte aligned device buffer");
-    const size_t need = batch_table_bytes(h0->p.storage, nmembers, tiles, waves);
+    const size_t need = batch_table_bytes(h0->p.storage, nmembers, tiles, rtiles, waves);
     if (work_bytes < need)
         return fail(LBM_VANS_EINVAL, "work has %zu bytes, %zu needed", work_bytes, need);
 
@@ -4754,6 +5095,9 @@ int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, voi
     b->d_tmap_adj = reinterpret_cast<int *>(w + align256(nmembers * dsz) +
                                             align256(tiles * sizeof(int)));
     size_t off = align256(nmembers * dsz) + 2 * align256(tiles * sizeof(int));
+    b->d_tmap_rev = reinterpret_cast<int *>(w + off);
+    off += align256(rtiles * sizeof(int));
+    for (int32_t k = 0; k < nmembers; k++) b->rev_ok = b->rev_ok && reverse_fits(members[k]->g);
     for (int q = 0; q < 4; q++) {
         b->d_wmap[q] = reinterpret_cast<int *>(w + off);
         off += align256(waves[q] * sizeof(int));
@@ -5044,8 +5388,21 @@ int lbm_vans_batch_grad(lbm_vans_batch *b, int32_t objective, int64_t nsteps,
                 r = batch_sweep(b, b->stream, src, seg_slot(j), res_on(&b->m[0]->p, s0 + j - 1));
                 if (r) return r;
             }
-            for (int64_t n = s1 - 1; n >= s0; n--) {
-                const int state = n == s0 ? ckpt_slot(c) : seg_slot(n - s0);
+            auto state_of = [&](int64_t n) { return n == s0 ? ckpt_slot(c) : seg_slot(n - s0); };
+            for (int64_t n = s1 - 1; b->rev_ok && n >= s0;) {
+                const int m = static_cast<int>(std::min<int64_t>(REV_STEPS, n - s0 + 1));
+                RevSlots slots{};
+                for (int k = 0; k < m; k++) {
+                    slots.slot[k] = state_of(n - k);
+                    slots.res |= (res_on(&b->m[0]->p, n - k) ? 1 : 0) << k;
+                }
+                r = batch_reverse(b, slots, m, a, 1 - a);
+                if (r) return r;
+                a = 1 - a;
+                n -= m;
+            }
+            for (int64_t n = s1 - 1; !b->rev_ok && n >= s0; n--) {
+                const int state = state_of(n);
                 r = batch_adjoint(b, false, state, a, 1 - a, res_on(&b->m[0]->p, n));
                 if (r) return r;
                 a = 1 - a;
