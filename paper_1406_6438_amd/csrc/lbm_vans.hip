@@ -1463,6 +1463,23 @@ __device__ __forceinline__ void static_while(F &&f)
     static_while_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// Whether the waves of a workgroup walk their rows in step (a barrier at each row; every
+// wave of a kernel takes the same number of them, one that has no chunk has ended): the
+// lines that neighbouring strips share at their seams are then read and written by both at
+// about the same time.  Periodic FP32 passes of three and four steps in chunks of 24 rows
+// and more.  GLUPS, without / with: 4096^2 box, four steps 213.3 / 221.7, 2048^2 172 / 173,
+// three steps 144 / 166; 16 periodic members 200 / 201, three steps 153 / 159 (a copy
+// kernel with the four-step access pattern and 250 columns per workgroup: 375 / 300 us).
+// Not for shorter chunks, which the barrier keeps from overlapping their starts and ends
+// (1024^2 in 12 rows 144 / 137, 6 rows 130 / 125), not with walls or ends, whose waves
+// differ in work (4096^2 with walls in y 193 / 183, closed 189 / 183, open channel 186.3 /
+// 185.0), and not in FP16, which does not gain (8192^2 box 233 to 234 / 231 to 237).
+template <typename S, int BX, bool WY, int NS, int NR>
+constexpr bool tb_lockstep()
+{
+    return std::is_same_v<S, float> && BX == 0 && !WY && NS >= 3 && NR >= 24;
+}
+
 // BXA: the x ends whose gather lookahead the pass takes (the kernel's own, also when a
 // wave of it runs without x-end rules, so that both paths fit its registers).
 template <typename S, typename R, int BX, bool WY, int NS, int NR, int BXA = BX>
@@ -1725,6 +1742,7 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
     middle2(0);
     static_while<NR>([&](auto jc) {
         constexpr int j = decltype(jc)::value;
+        if constexpr (BXA == 0 && tb_lockstep<S, BX, WY, NS, NR>()) __builtin_amdgcn_s_barrier();
         finish(j + H);
         if constexpr (j + H + PD <= NR + H - 1) issue(j + H + PD);
         if constexpr (j + 2 * H + 2 + PD < NE) eps_row(j + 2 * H + 2 + PD);
@@ -1799,7 +1817,7 @@ __device__ __forceinline__ void sweep_multi(const S *__restrict__ fin, S *__rest
     const int wid = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * NW +
                                                    threadIdx.x / TX);
     const int strip = wid % nstrips, chunk = wid / nstrips;
-    if (chunk >= nchunks) return;              // whole waves only; no barrier below
+    if (chunk >= nchunks) return;              // whole waves (an ended one is not waited for)
     tb_wave_x<S, R, BX, WY, NS, NR>(fin, fout, eps, g, ph, strip, chunk, res_a);
 }
 
@@ -3109,7 +3127,7 @@ __device__ __forceinline__ void batch_multi_wave(const Member<R> *__restrict__ M
 {
     const int wid = __builtin_amdgcn_readfirstlane(xcd_tile(blockIdx.x, gridDim.x) * NW +
                                                    threadIdx.x / TX);
-    if (wid >= nwaves) return;                 // whole waves only; no barrier below
+    if (wid >= nwaves) return;                 // whole waves (an ended one is not waited for)
     const Member<R> &d = M[wmap[wid]];
     const Geo g = d.g;
     Phys<R> ph = d.ph;
