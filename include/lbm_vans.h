@@ -347,7 +347,12 @@ typedef struct lbm_vans_batch_config {
                              least as many waves of the batched four-step pass as
                              the GPU holds of it, else 3): with LBM_F32 /
                              LBM_F16_SHIFTED storage the multi-step pass over every
-                             member; vec and grid apply to single steps           */
+                             member; vec and grid apply to single steps.  With 0
+                             and pass_rows = 0, LBM_F32_SHIFTED batches of at most
+                             2^21 nodes that do not take the four-step pass, and
+                             with grid = 0 and the widest vec LBM_F64 batches, run
+                             up to three single steps per launch on tiles (the
+                             autotuner does not time these)                        */
     int32_t pass_rows;    /* rows per chunk of the batched three-step pass, 24 or 28
                              with FP32 storage (0 = automatic: 28 when the whole
                              batch has four times as many waves of 28 rows as the

@@ -1786,8 +1786,9 @@ __device__ __forceinline__ void tb_wave_x(const S *__restrict__ fin, S *__restri
                                           const Phys<R> &ph, int strip, int chunk, int res_a)
 {
     // the wall-free third path only where it leaves the kernel's waves per SIMD as
-    // they are (the lone four-step and FP16 kernels drop to one wave with it)
-    constexpr bool YCLEAR = WY && (BATCH || (NS == 3 && std::is_same_v<S, float>));
+    // they are (the lone FP16 kernels drop to one wave with it; FP32 without / with it in
+    // the lone four-step pass, GLUPS: 4096^2 open channel 185.9 / 192.2, 2048^2 140 / 143)
+    constexpr bool YCLEAR = WY && (BATCH || (NS >= 3 && std::is_same_v<S, float>));
     // the batched three-step kernel keeps one path (with the others it measured 142
     // against 154 GLUPS)
     constexpr bool XCLEAR = BX == 2 && !(BATCH && NS == 3);
@@ -1874,19 +1875,17 @@ constexpr int TILE_H = 16;   // rows of a tile (columns: 16 or 32)
 // the nodes it recomputes (2048^2 FP64, three steps: 1.6 times the lattice's nodes, 63 us a
 // step against 104 of the one-step sweep, which moves 152 B per node at 6.1 TB/s).
 // all: when not 0, the state of every step s is stored, at fout + s all (elements).
+// h: the rings discarded, ns - 1 or more; (bx, by): the tile.
 template <typename S, typename R, int BX, bool WY, int TW, int TH>
-__global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(4))) void k_sweep_tile(const S *__restrict__ fin,
-                                                       S *__restrict__ fout,
-                                                       const R *__restrict__ eps, Geo g,
-                                                       Phys<R> ph, int ns, int ntx,
-                                                       long long all)
+__device__ __forceinline__ void tile_steps(const S *__restrict__ fin, S *__restrict__ fout,
+                                           const R *__restrict__ eps, const Geo &g, Phys<R> ph,
+                                           int ns, int h, int bx, int by, long long all,
+                                           R (*buf)[8][TH * TW])
 {
     constexpr bool WX = BX != 0;
-    __shared__ R buf[2][8][TH * TW];
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
-    const int h = ns - 1, tid = threadIdx.x, tx = tid % TW, ty = tid / TW;
-    const int xu = (t % ntx) * (TW - 2 * h) - h + tx;   // unwrapped node
-    const int yu = (t / ntx) * (TH - 2 * h) - h + ty;
+    const int tid = threadIdx.x, tx = tid % TW, ty = tid / TW;
+    const int xu = bx * (TW - 2 * h) - h + tx;   // unwrapped node
+    const int yu = by * (TH - 2 * h) - h + ty;
     // wrapped (once, unless the axis is shorter than a tile), or clamped behind an end
     auto inside = [](int v, int L, bool wall, int T) {
         if (wall) return min(max(v, 0), L - 1);
@@ -1949,13 +1948,13 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(4))) voi
         update_node_q<R, false, false, true, true>(d, P, q, wym, wyp, ores && wxm, ores && wxp, ph,
                                                    nullptr, false);
         ores = BX == 2;
-        if (all || s == h) {
+        if (all || s == ns - 1) {
             if (out) {
                 S *o = fout + s * all + (q0 + c0);
 #pragma unroll
                 for (int i = 0; i < 9; i++) o[i * g.plane] = d[i];
             }
-            if (s == h) return;                // uniform over the workgroup
+            if (s == ns - 1) return;                // uniform over the workgroup
         }
         R(*b)[TH * TW] = buf[s & 1];
 #pragma unroll
@@ -1972,6 +1971,17 @@ __global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(4))) voi
         d[8] = b[7][rp + xm];
         if (WX || WY) bounce(d, own);
     }
+}
+
+template <typename S, typename R, int BX, bool WY, int TW, int TH>
+__global__ __launch_bounds__(TW *TH) __attribute__((amdgpu_waves_per_eu(4)))
+void k_sweep_tile(const S *__restrict__ fin, S *__restrict__ fout, const R *__restrict__ eps,
+                  Geo g, Phys<R> ph, int ns, int ntx, long long all)
+{
+    __shared__ R buf[2][8][TH * TW];
+    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    tile_steps<S, R, BX, WY, TW, TH>(fin, fout, eps, g, ph, ns, ns - 1, t % ntx, t / ntx, all,
+                                     buf);
 }
 
 // Macroscopic fields of the current state (no collision, no store of populations), V
@@ -2567,8 +2577,8 @@ __global__ __launch_bounds__(NTHREADS) void k_adjoint_seed(const S *__restrict__
 }
 
 // One reverse step (no seed) with each wave walking K consecutive rows of a
-// 64-column strip, top to bottom: planes of 2^31 bytes or more in FP64, past the 32-bit
-// offsets of the reverse tiles.  The loads of row r + 1 (its adjoints, its
+// 64-column strip, top to bottom: planes past the 32-bit offsets of the reverse tiles (2^31
+// bytes in FP64), and large lone lattices in FP64 (grad_tiles).  The loads of row r + 1 (its adjoints, its
 // gather, its accumulators and the porosity row above it) are issued before the
 // arithmetic of row r, so that a row's FP64 arithmetic runs under the memory
 // latency of the next one instead of after it.  A node's porosity window is
@@ -3045,6 +3055,7 @@ struct Member {
     int tile0;              // first position in the sweep tile list of its width
     int tile0_adj;          // first position in the adjoint tile list
     int tile0_rev, rev_tx;  // first position in the reverse tile list, tiles in x
+    int tile0_bt, bt_tx;    // first position in the step tile list, tiles in x
     int tb_strips[3];       // strips of the two-, three- and four-step passes
     int tw0[4];             // first position in the wave lists of the two-step pass, of
                             // the three-step pass in short and in tall chunks, and of
@@ -3115,6 +3126,31 @@ __global__ __launch_bounds__(NTHREADS) void k_batch_sweep(const Member<R> *__res
             reinterpret_cast<S *>(state_slot(d, dst)), d.eps, gs, ph, nullptr, T - d.tile0);
         __syncthreads();  // a next tile of this block reuses the LDS porosity tile
     }
+}
+
+// ns (1 .. BT_STEPS) single steps of every member in one launch, one workgroup per entry of
+// the step tile list; all: the state of every step s goes to the slot dst + s (gradient
+// workspace).  As the lone tile kernel, with the halo of BT_STEPS steps for any ns (one tile
+// list).
+constexpr int BT_W = 32, BT_STEPS = 3;
+constexpr int BT_OW = BT_W - 2 * (BT_STEPS - 1), BT_OH = TILE_H - 2 * (BT_STEPS - 1);
+
+template <typename S, typename R, int BX, bool WY>
+__global__ __launch_bounds__(BT_W *TILE_H) __attribute__((amdgpu_waves_per_eu(4)))
+void k_batch_tile(const Member<R> *__restrict__ M, const int *__restrict__ tmap, int ntiles,
+                  int src, int dst, int ns, int reservoir, int all)
+{
+    __shared__ R buf[2][8][BT_W * TILE_H];
+    const int T = xcd_tile(blockIdx.x, ntiles);
+    const Member<R> &d = M[tmap[T]];
+    const Geo g = d.g;
+    Phys<R> ph = d.ph;
+    ph.reservoir = reservoir;
+    const int t = T - d.tile0_bt;
+    tile_steps<S, R, BX, WY, BT_W, TILE_H>(
+        reinterpret_cast<const S *>(state_slot(d, src)),
+        reinterpret_cast<S *>(state_slot(d, dst)), d.eps, g, ph, ns, BT_STEPS - 1, t % d.bt_tx,
+        t / d.bt_tx, all ? d.gpop / static_cast<long long>(sizeof(S)) : 0, buf);
 }
 
 // NS steps of every member in one pass (the multi-step pass, one wave per
@@ -3960,21 +3996,36 @@ int launch_tile(lbm_vans_handle *h, const void *src, void *dst, int64_t n, int n
     });
 }
 
-// Steps the next launch takes of `steps` that remain (no diagnostics among them).
-int next_pass(const lbm_vans_handle *h, int64_t steps)
+// Whether the gradient's forward and recomputed states come from the tile kernel (in FP64
+// both or neither: the same bits for any checkpoint interval), and in FP64 its reverse steps
+// from the reverse tiles.  Not for FP64 lattices above 2^19 nodes, where the recompute and
+// the reverse step beside it on the other stream contend for the FP64 units and the rings'
+// arithmetic costs more than the bytes saved (us per step of the whole gradient, one-step
+// launches and rows / tiles: 512 x 300 29.9 / 20.8, 1024 x 512 60.3 / 57.2, 1024^2 109.6 /
+// 110.4, 2048 x 1024 220 / 224, with the reverse alone on tiles 221 / 238; FP32 2048 x 1024
+// 118 / 115, 4096 x 2048 471 / 461).
+bool grad_tiles(const lbm_vans_handle *h)
+{
+    return h->tile_ns && (h->p.storage != LBM_F64 ||
+                          static_cast<long long>(h->p.Lx) * h->p.Ly <= (1LL << 19));
+}
+
+// Steps the next launch takes of `steps` that remain (no diagnostics among them); tile: the
+// tile kernel may take them.
+int next_pass(const lbm_vans_handle *h, int64_t steps, bool tile = true)
 {
     const int m = step_pass(h);
-    return static_cast<int>(std::min<int64_t>(h->tile_on ? h->tile_ns : m, steps));
+    return static_cast<int>(std::min<int64_t>(h->tile_on && tile ? h->tile_ns : m, steps));
 }
 
 // One launch of m steps (next_pass) from the handle's current state into its other buffer;
 // the handle's state slot and step count advance.
-int launch_pass(lbm_vans_handle *h, int m)
+int launch_pass(lbm_vans_handle *h, int m, bool tile = true)
 {
     const void *src = h->buf[h->cur];
     void *dst = h->buf[1 - h->cur];
     int rc;
-    if (h->tile_on) rc = launch_tile(h, src, dst, h->n, m, 0, h->stream);
+    if (h->tile_on && tile) rc = launch_tile(h, src, dst, h->n, m, 0, h->stream);
     else if (m >= 2) rc = launch_multi(h, src, dst, m);
     else rc = launch_sweep(h, false);
     if (rc) return rc;
@@ -4379,6 +4430,10 @@ GradLayout grad_layout(const lbm_vans_params *p, int64_t nsteps, int32_t ckpt_ev
     return G;
 }
 
+// Step tiles of a batch's member.
+int batch_tiles_x(const Geo &g) { return (g.Lx + BT_OW - 1) / BT_OW; }
+int batch_tiles(const Geo &g) { return batch_tiles_x(g) * ((g.Ly + BT_OH - 1) / BT_OH); }
+
 // Whether the reverse tiles' 32-bit byte offsets reach every node of a plane (FP64).
 bool reverse_fits(const Geo &g) { return g.plane * 8 < (1LL << 31); }
 
@@ -4451,13 +4506,14 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
         if (r) return r;
         h->cur = 0;
         h->n = 0;
+        const bool tiles = grad_tiles(h);
         for (int64_t s0 = 0; s0 < nsteps || s0 == 0; s0 += K) {
             HIP_TRY(hipMemcpyAsync(ckpt(s0 / K), h->buf[h->cur], G.pop, hipMemcpyDeviceToDevice,
                                    h->stream));
             // only the checkpoints are kept: several steps per launch in between
             for (int64_t k = 0; k < K && s0 + k < nsteps;) {
-                const int m = next_pass(h, std::min<int64_t>(K - k, nsteps - s0 - k));
-                r = launch_pass(h, m);
+                const int m = next_pass(h, std::min<int64_t>(K - k, nsteps - s0 - k), tiles);
+                r = launch_pass(h, m, tiles);
                 if (r) return r;
                 k += m;
             }
@@ -4507,8 +4563,8 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
         const int adj_chunks = (g.Ly + ADJ_ROWS - 1) / ADJ_ROWS;
         const unsigned adj_blocks =
             static_cast<unsigned>(((long long)adj_strips * adj_chunks + NW - 1) / NW);
-        // where a plane's bytes do not fit the tiles' 32-bit offsets
-        const bool rev = reverse_fits(g);
+        // else the row-walking reverse step
+        const bool rev = reverse_fits(g) && (tiles || h->p.storage != LBM_F64);
         hipStream_t rs = two ? h->stream2 : h->stream;
         auto recompute = [&](int64_t c) -> int {
             const int64_t s0 = c * K, s1 = std::min<int64_t>(s0 + K, nsteps);
@@ -4516,7 +4572,7 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
             for (int64_t j = 1; j < s1 - s0;) {
                 const void *src = j == 1 ? (const void *)ckpt(c) : (const void *)seg(set, j - 1);
                 int m = 1, rr;
-                if (h->tile_ns) {              // every state of a launch is kept
+                if (tiles) {                   // every state of a launch is kept
                     m = static_cast<int>(std::min<int64_t>(h->tile_ns, s1 - s0 - j));
                     rr = launch_tile(h, src, seg(set, j), s0 + j - 1, m, G.pop, rs);
                 } else {
@@ -4661,16 +4717,19 @@ struct lbm_vans_batch {
     lbm_vans_batch_config cfg{};
     size_t desc_bytes = 0;          // bytes of one device descriptor
     std::vector<char> desc;         // host image of the descriptors
-    std::vector<int> tmap, tmap_adj, tmap_rev;  // tile lists of the sweep, the adjoint's seed
-                                                // and the reverse steps
+    std::vector<int> tmap, tmap_adj, tmap_rev, tmap_bt;  // tile lists of the sweep, the adjoint's
+                                                         // seed, the reverse steps and the
+                                                         // single steps on tiles
     std::vector<int> wmap[4];         // wave lists of the two-step pass, of the three-step
                                       // pass in short and in tall chunks (FP32 only) and of
                                       // the four-step pass (FP32 only)
     void *d_desc = nullptr;
-    int *d_tmap = nullptr, *d_tmap_adj = nullptr, *d_tmap_rev = nullptr,
+    int *d_tmap = nullptr, *d_tmap_adj = nullptr, *d_tmap_rev = nullptr, *d_tmap_bt = nullptr,
         *d_wmap[4] = {nullptr, nullptr, nullptr, nullptr};
-    int ntiles = 0, ntiles_adj = 0, ntiles_rev = 0, nwaves[4] = {0, 0, 0, 0};
+    int ntiles = 0, ntiles_adj = 0, ntiles_rev = 0, ntiles_bt = 0, nwaves[4] = {0, 0, 0, 0};
     bool rev_ok = true;             // every member fits the reverse tiles' addressing
+    bool bt_ok = false;             // ... and the step tiles' (FP64 and FP32 storage)
+    long long nodes = 0;            // of all members
     bool multi_ok = true;           // every member fits the multi-step passes' addressing
     bool multi4_ok = false;         // ... and the four-step pass (FP32, rows)
     long long tall_resident = 0;    // waves of the tall batched three-step kernel the chip holds
@@ -4681,11 +4740,11 @@ struct lbm_vans_batch {
 namespace {
 
 size_t batch_table_bytes(int storage, size_t nmembers, size_t ntiles_adj, size_t ntiles_rev,
-                         const size_t *nwaves)
+                         size_t ntiles_bt, const size_t *nwaves)
 {
     const size_t d = storage == LBM_F64 ? sizeof(Member<double>) : sizeof(Member<float>);
     return align256(nmembers * d) + 2 * align256(ntiles_adj * sizeof(int)) +
-           align256(ntiles_rev * sizeof(int)) +
+           align256(ntiles_rev * sizeof(int)) + align256(ntiles_bt * sizeof(int)) +
            align256(nwaves[0] * sizeof(int)) + align256(nwaves[1] * sizeof(int)) +
            align256(nwaves[2] * sizeof(int)) + align256(nwaves[3] * sizeof(int));
 }
@@ -4730,6 +4789,7 @@ int batch_upload(lbm_vans_batch *b, int vec, char *gw, int64_t nsteps, int32_t c
     b->tmap.clear();
     b->tmap_adj.clear();
     b->tmap_rev.clear();
+    b->tmap_bt.clear();
     for (auto &wm : b->wmap) wm.clear();
     int rc = with_types(b->storage, [&](auto *sp, auto *rp) -> int {
         using R = std::remove_pointer_t<decltype(rp)>;
@@ -4759,6 +4819,9 @@ int batch_upload(lbm_vans_batch *b, int vec, char *gw, int64_t nsteps, int32_t c
             d.tile0_rev = static_cast<int>(b->tmap_rev.size());
             d.rev_tx = reverse_tiles_x(d.g);
             b->tmap_rev.insert(b->tmap_rev.end(), reverse_tiles(d.g), static_cast<int>(k));
+            d.tile0_bt = static_cast<int>(b->tmap_bt.size());
+            d.bt_tx = batch_tiles_x(d.g);
+            b->tmap_bt.insert(b->tmap_bt.end(), batch_tiles(d.g), static_cast<int>(k));
             for (int q = 0; q < 4; q++) {
                 const int ns = q == 0 ? 2 : (q < 3 ? 3 : 4);
                 const int cols = TX - 2 * (ns - 1);
@@ -4791,6 +4854,7 @@ int batch_upload(lbm_vans_batch *b, int vec, char *gw, int64_t nsteps, int32_t c
     b->ntiles = static_cast<int>(b->tmap.size());
     b->ntiles_adj = static_cast<int>(b->tmap_adj.size());
     b->ntiles_rev = static_cast<int>(b->tmap_rev.size());
+    b->ntiles_bt = static_cast<int>(b->tmap_bt.size());
     for (int q = 0; q < 4; q++) b->nwaves[q] = static_cast<int>(b->wmap[q].size());
     HIP_TRY(hipMemcpyAsync(b->d_desc, b->desc.data(), b->desc.size(), hipMemcpyHostToDevice,
                            b->stream));
@@ -4799,6 +4863,8 @@ int batch_upload(lbm_vans_batch *b, int vec, char *gw, int64_t nsteps, int32_t c
     HIP_TRY(hipMemcpyAsync(b->d_tmap_adj, b->tmap_adj.data(), b->tmap_adj.size() * sizeof(int),
                            hipMemcpyHostToDevice, b->stream));
     HIP_TRY(hipMemcpyAsync(b->d_tmap_rev, b->tmap_rev.data(), b->tmap_rev.size() * sizeof(int),
+                           hipMemcpyHostToDevice, b->stream));
+    HIP_TRY(hipMemcpyAsync(b->d_tmap_bt, b->tmap_bt.data(), b->tmap_bt.size() * sizeof(int),
                            hipMemcpyHostToDevice, b->stream));
     for (int q = 0; q < 4; q++)
         if (!b->wmap[q].empty())
@@ -4906,17 +4972,67 @@ int batch_max_pass(const lbm_vans_batch *b)
     return m == 4 && !b->multi4_ok ? 3 : m;
 }
 
-// One batched launch of m steps (the one-step sweep for m = 1).
+// ns (1 .. BT_STEPS) single steps of every member on tiles, from state slot src to dst (all:
+// every step's state, to dst, dst + 1, ...).
+int batch_tile(lbm_vans_batch *b, hipStream_t st, int src, int dst, int res_a, int ns, bool all)
+{
+    return with_types(b->storage, [&](auto *sp, auto *rp) -> int {
+        using S = std::remove_pointer_t<decltype(sp)>;
+        using R = std::remove_pointer_t<decltype(rp)>;
+        if constexpr (std::is_same_v<S, _Float16>) {
+            return fail(LBM_VANS_EINVAL, "the tile kernel needs FP64 or FP32 storage");
+        } else {
+            with_bxwy(b->bx, b->wy, [&](auto bxc, auto wyc) {
+                hipLaunchKernelGGL((k_batch_tile<S, R, decltype(bxc)::value,
+                                                 decltype(wyc)::value>),
+                                   dim3(b->ntiles_bt), dim3(BT_W * TILE_H), 0, st,
+                                   static_cast<const Member<R> *>(b->d_desc),
+                                   (const int *)b->d_tmap_bt, b->ntiles_bt, src, dst, ns, res_a,
+                                   all ? 1 : 0);
+            });
+            return check_launch("k_batch_tile");
+        }
+    });
+}
+
+// Whether the batch's single steps may go on tiles: automatic steps per launch, and in FP64,
+// which has single steps only, no shape of theirs asked for either.
+bool batch_tile_any(const lbm_vans_batch *b)
+{
+    return b->bt_ok && b->cfg.steps_per_pass == 0 && b->cfg.pass_rows == 0 &&
+           (b->storage != LBM_F64 || (b->cfg.grid == 0 && b->cfg.vec == b->vmax));
+}
+
+// Whether its steps do: FP64, and FP32 batches too small for the four-step pass and of at
+// most BT_NODES nodes.  FP32, us per step of channels of 256 to 1024 columns on three-step
+// passes / tiles, by nodes in all: 0.01M 13.5 / 1.9, 0.15M 13.8 / 2.6, 0.98M 14.8 / 8.7, 1.33M
+// 15.3 / 12.1, 2.22M 20.0 / 17.3, 2.70M 20.4 / 21.0.
+constexpr long long BT_NODES = 1LL << 21;
+bool batch_tile_on(const lbm_vans_batch *b)
+{
+    return batch_tile_any(b) && (b->storage == LBM_F64 || batch_max_pass(b) == 1 ||
+                                 (batch_max_pass(b) == 3 && b->nodes <= BT_NODES));
+}
+
+// Steps the next batched launch takes of `steps` that remain.
+int batch_next(const lbm_vans_batch *b, int64_t steps)
+{
+    return static_cast<int>(
+        std::min<int64_t>(batch_tile_on(b) ? BT_STEPS : batch_max_pass(b), steps));
+}
+
+// One batched launch of m steps (batch_next).
 int batch_launch(lbm_vans_batch *b, hipStream_t st, int src, int res_a, int m)
 {
+    if (batch_tile_on(b)) return batch_tile(b, st, src, 1 - src, res_a, m, false);
     return m >= 2 ? batch_multi(b, st, src, 1 - src, res_a, m)
                   : batch_sweep(b, st, src, 1 - src, res_a);
 }
 
-// Launches of a run of `steps` steps, each as many as batch_max_pass allows.
+// Launches of a run of `steps` steps, each as many as batch_next gives.
 int64_t batch_launch_count(const lbm_vans_batch *b, int64_t steps)
 {
-    const int mp = batch_max_pass(b);
+    const int mp = batch_next(b, steps);
     return (steps + mp - 1) / mp;
 }
 
@@ -4964,10 +5080,9 @@ int batch_capture(lbm_vans_batch *b, int s0)
     hipGraph_t graph = nullptr;
     HIP_TRY(hipStreamBeginCapture(b->cap, hipStreamCaptureModeThreadLocal));
     int rc = LBM_VANS_OK;
-    const int mp = batch_max_pass(b);
     int src = s0;
     for (int j = 0; j < b->cfg.graph_steps && !rc; src = 1 - src) {
-        const int m = std::min(mp, b->cfg.graph_steps - j);
+        const int m = batch_next(b, b->cfg.graph_steps - j);
         rc = batch_launch(b, b->cap, src, 1, m);
         j += m;
     }
@@ -5037,14 +5152,15 @@ extern "C" {
 size_t lbm_vans_batch_work_bytes(lbm_vans_handle *const *members, int32_t nmembers)
 {
     if (!members || nmembers < 1) return 0;
-    size_t tiles = 0, rtiles = 0, waves[4] = {0, 0, 0, 0};
+    size_t tiles = 0, rtiles = 0, btiles = 0, waves[4] = {0, 0, 0, 0};
     for (int32_t k = 0; k < nmembers; k++) {
         if (!members[k]) return 0;
         tiles += static_cast<size_t>(members[k]->g.ntiles);
         rtiles += static_cast<size_t>(reverse_tiles(members[k]->g));
+        btiles += static_cast<size_t>(batch_tiles(members[k]->g));
         for (int q = 0; q < 4; q++) waves[q] += batch_waves(&members[k]->p, q);
     }
-    return batch_table_bytes(members[0]->p.storage, nmembers, tiles, rtiles, waves);
+    return batch_table_bytes(members[0]->p.storage, nmembers, tiles, rtiles, btiles, waves);
 }
 
 int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, void *work,
@@ -5056,7 +5172,7 @@ int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, voi
     if (!members || nmembers < 1) return fail(LBM_VANS_EINVAL, "no members");
     const lbm_vans_handle *h0 = members[0];
     if (!h0) return fail(LBM_VANS_EINVAL, "member 0 is NULL");
-    size_t tiles = 0, rtiles = 0, waves[4] = {0, 0, 0, 0};
+    size_t tiles = 0, rtiles = 0, btiles = 0, waves[4] = {0, 0, 0, 0};
     for (int32_t k = 0; k < nmembers; k++) {
         const lbm_vans_handle *h = members[k];
         if (!h) return fail(LBM_VANS_EINVAL, "member %d is NULL", k);
@@ -5073,6 +5189,7 @@ int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, voi
                         (long long)h->n, (long long)h0->n);
         tiles += static_cast<size_t>(h->g.ntiles);
         rtiles += static_cast<size_t>(reverse_tiles(h->g));
+        btiles += static_cast<size_t>(batch_tiles(h->g));
         for (int q = 0; q < 4; q++) waves[q] += batch_waves(&h->p, q);
     }
     if (std::max(tiles, rtiles) > static_cast<size_t>(INT32_MAX))
@@ -5082,7 +5199,7 @@ int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, voi
         return fail(LBM_VANS_EINVAL, "%zu waves: too many for one launch", wmax);
     if (!work || reinterpret_cast<uintptr_t>(work) % 256)
         return fail(LBM_VANS_EINVAL, "work must be a 256-byte aligned device buffer");
-    const size_t need = batch_table_bytes(h0->p.storage, nmembers, tiles, rtiles, waves);
+    const size_t need = batch_table_bytes(h0->p.storage, nmembers, tiles, rtiles, btiles, waves);
     if (work_bytes < need)
         return fail(LBM_VANS_EINVAL, "work has %zu bytes, %zu needed", work_bytes, need);
 
@@ -5115,7 +5232,15 @@ int lbm_vans_batch_create(lbm_vans_handle *const *members, int32_t nmembers, voi
     size_t off = align256(nmembers * dsz) + 2 * align256(tiles * sizeof(int));
     b->d_tmap_rev = reinterpret_cast<int *>(w + off);
     off += align256(rtiles * sizeof(int));
-    for (int32_t k = 0; k < nmembers; k++) b->rev_ok = b->rev_ok && reverse_fits(members[k]->g);
+    b->d_tmap_bt = reinterpret_cast<int *>(w + off);
+    off += align256(btiles * sizeof(int));
+    b->bt_ok = b->storage != LBM_F16_SHIFTED;
+    for (int32_t k = 0; k < nmembers; k++) {
+        const Geo &g = members[k]->g;
+        b->rev_ok = b->rev_ok && reverse_fits(g);
+        b->bt_ok = b->bt_ok && g.plane * elem_bytes(b->storage) < (1LL << 31);
+        b->nodes += static_cast<long long>(g.Lx) * g.Ly;
+    }
     for (int q = 0; q < 4; q++) {
         b->d_wmap[q] = reinterpret_cast<int *>(w + off);
         off += align256(waves[q] * sizeof(int));
@@ -5270,7 +5395,7 @@ int lbm_vans_batch_step(lbm_vans_batch *b, int64_t nsteps)
             batch_advance(b, C, batch_launch_count(b, C));
             k += C;
         } else {
-            const int m = static_cast<int>(std::min<int64_t>(batch_max_pass(b), nsteps - k));
+            const int m = batch_next(b, nsteps - k);
             rc = batch_launch(b, b->stream, cur, res_on(&b->m[0]->p, n), m);
             if (rc) return rc;
             batch_advance(b, m, 1);
@@ -5354,8 +5479,7 @@ int lbm_vans_batch_grad(lbm_vans_batch *b, int32_t objective, int64_t nsteps,
             // three per launch
             for (int64_t j = 0; j < K && s0 + j < nsteps;) {
                 const int cur = b->m[0]->cur;
-                const int m = static_cast<int>(
-                    std::min<int64_t>({(int64_t)batch_max_pass(b), K - j, nsteps - s0 - j}));
+                const int m = batch_next(b, std::min<int64_t>(K - j, nsteps - s0 - j));
                 r = batch_launch(b, b->stream, cur, res_on(&b->m[0]->p, b->m[0]->n), m);
                 if (r) return r;
                 batch_advance(b, m, 1);
@@ -5401,10 +5525,18 @@ int lbm_vans_batch_grad(lbm_vans_batch *b, int32_t objective, int64_t nsteps,
         const int64_t nck = nsteps == 0 ? 0 : (nsteps + K - 1) / K;
         for (int64_t c = nck - 1; c >= 0; c--) {
             const int64_t s0 = c * K, s1 = std::min<int64_t>(s0 + K, nsteps);
-            for (int64_t j = 1; j < s1 - s0; j++) {
+            for (int64_t j = 1; j < s1 - s0;) {
                 const int src = j == 1 ? ckpt_slot(c) : seg_slot(j - 1);
-                r = batch_sweep(b, b->stream, src, seg_slot(j), res_on(&b->m[0]->p, s0 + j - 1));
+                const int res = res_on(&b->m[0]->p, s0 + j - 1);
+                int m = 1;
+                if (batch_tile_any(b)) {       // every state of a launch is kept
+                    m = static_cast<int>(std::min<int64_t>(BT_STEPS, s1 - s0 - j));
+                    r = batch_tile(b, b->stream, src, seg_slot(j), res, m, true);
+                } else {
+                    r = batch_sweep(b, b->stream, src, seg_slot(j), res);
+                }
                 if (r) return r;
+                j += m;
             }
             auto state_of = [&](int64_t n) { return n == s0 ? ckpt_slot(c) : seg_slot(n - s0); };
             for (int64_t n = s1 - 1; b->rev_ok && n >= s0;) {
