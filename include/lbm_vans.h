@@ -162,7 +162,8 @@ typedef struct lbm_vans_params {
                               (also with diag_every > 0, between the states recorded),
                               FP64 and FP32 lattices take up to six single steps per
                               launch, on tiles that exchange the states of every step
-                              as stored (the same bits however steps are grouped).    */
+                              as stored (the same bits as the one-step sweep's, however
+                              steps are grouped, recorded or not).                    */
     int32_t pass_rows;     /* output rows per chunk (wave) of the three-step pass:
                               0 = automatic; LBM_F32_SHIFTED: 6, 12, 24 or 28
                               (automatic: the tallest whose waves still fill the GPU;

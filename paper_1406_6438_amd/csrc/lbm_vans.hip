@@ -329,16 +329,28 @@ __device__ __forceinline__ R sqroot(R x)
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
+// FUSED (from here on): every fused operation is written out and the compiler forms no
+// others.  Left to itself it fuses the same expression one way or another by what stands
+// beside it (of two products that are added it takes either, and products formed once before
+// a loop stay products), and the kernels that take single steps, the one-step sweep and the
+// tiles, would differ in their last bits.
+
 // Darcy and Forchheimer coefficients a = eps^2 nu / K, b = eps^3 F_eps / sqrt(K)
 // of the drag law, one branch-free form for both closures:
 //   a = ca (1-eps)^2 / eps + ka eps^2,   b = cb (1-eps) + kb eps^3.
 // Ergun closure: ca = 150 nu / d_p^2, cb = 1.75 / d_p, ka = kb = 0 (a = b = 0 at
 // eps = 1); constant K, F_eps: ka = nu / K, kb = F_eps / sqrt(K), ca = cb = 0; all
 // four 0 without drag.  inv_eps = 1 / eps.
-template <typename R>
+template <typename R, bool FUSED = false>
 __device__ __forceinline__ void drag_coeffs(const Phys<R> &ph, R eps, R inv_eps, R &a, R &b)
 {
     const R s = R(1) - eps, e2 = eps * eps;
+    if constexpr (FUSED) {
+#pragma clang fp contract(off)
+        a = fma_(ph.ka, e2, ph.ca * s * s * inv_eps);
+        b = fma_(ph.cb, s, ph.kb * e2 * eps);
+        return;
+    }
     a = ph.ca * s * s * inv_eps + ph.ka * e2;
     b = ph.cb * s + ph.kb * e2 * eps;
 }
@@ -372,7 +384,7 @@ struct EpsTerms {
     R e, ie, gex, gey, a, b;
 };
 
-template <typename R>
+template <typename R, bool FUSED = false>
 __device__ __forceinline__ EpsTerms<R> eps_terms(R eps, R gex, R gey, const Phys<R> &ph)
 {
     EpsTerms<R> q;
@@ -380,7 +392,7 @@ __device__ __forceinline__ EpsTerms<R> eps_terms(R eps, R gex, R gey, const Phys
     q.ie = rcp(eps);
     q.gex = gex;
     q.gey = gey;
-    drag_coeffs(ph, eps, q.ie, q.a, q.b);
+    drag_coeffs<R, FUSED>(ph, eps, q.ie, q.a, q.b);
     return q;
 }
 
@@ -391,15 +403,35 @@ __device__ __forceinline__ NodeFwd<R> node_forward_m(R dS, R mx, R my, const Eps
     NodeFwd<R> F;
     Node<R> &N = F.N;
     N.dS = dS;
-    N.S = FUSED ? fma_(q.e, ph.rho0, N.dS) : q.e * ph.rho0 + N.dS;
     N.mx = mx;
     N.my = my;
     F.ie = q.ie;
-    N.rho = N.S * F.ie;
-    const R third = R(1) / R(3);
-    const R Qx = third * N.rho * q.gex, Qy = third * N.rho * q.gey;
     F.a = q.a;
     F.b = q.b;
+    const R third = R(1) / R(3);
+    if constexpr (FUSED) {
+#pragma clang fp contract(off)
+        N.S = fma_(q.e, ph.rho0, dS);
+        N.rho = N.S * q.ie;
+        const R c = third * N.rho;
+        const R Qx = fma_(c, q.gex, ph.Gx), Qy = fma_(c, q.gey, ph.Gy);   // Q + G
+        F.Vx = fma_(R(0.5), Qx, mx);
+        F.Vy = fma_(R(0.5), Qy, my);
+        F.A = fma_(R(0.5), q.a, N.S);
+        F.Vn = sqroot(fma_(F.Vx, F.Vx, F.Vy * F.Vy));
+        F.Rr = sqroot(fma_(F.A, F.A, (R(2) * q.b) * F.Vn));
+        F.k = R(2) * rcp(F.A + F.Rr);
+        N.ux = F.k * F.Vx;
+        N.uy = F.k * F.Vy;
+        F.un = F.k * F.Vn;
+        F.drag = fma_(q.b, F.un, q.a);
+        N.Tx = fma_(-F.drag, N.ux, Qx);
+        N.Ty = fma_(-F.drag, N.uy, Qy);
+        return F;
+    }
+    N.S = q.e * ph.rho0 + N.dS;
+    N.rho = N.S * F.ie;
+    const R Qx = third * N.rho * q.gex, Qy = third * N.rho * q.gey;
     F.Vx = N.mx + R(0.5) * (Qx + ph.Gx);
     F.Vy = N.my + R(0.5) * (Qy + ph.Gy);
     F.A = N.S + R(0.5) * F.a;
@@ -460,28 +492,42 @@ __device__ constexpr int CY[9] = {0, 0, 1, 0, -1, 1, 1, -1, -1};
 // The middle term is even and the last one odd under e_i -> -e_i, so each pair of
 // opposite directions shares them.  The stored value is d*_i - w_i de_i with
 // de_i = (rho0/2) (eps(x + e_i) - eps(x)), the link-midpoint shift (0 when the
-// value bounces back).
-// value bounces back).  FUSED: the shift is one fused operation (hr D_i, hr = rho0 / 2), so
-// that where the porosity does not change from step to step its products do not become
-// roundings of their own in some steps and not in others.
+// value bounces back); with FUSED it is one fused operation (hr D_i, hr = rho0 / 2).
 template <typename R, bool FUSED = false>
 __device__ __forceinline__ void collide(R d[9], const Node<R> &N, const Phys<R> &ph,
                                         const R de[9], R hr, const R D[9])
 {
     const R om = ph.omega, omc = R(1) - ph.omega, P = ph.pre;
+    const R w0 = R(4) / R(9), w1 = R(1) / R(9), w2 = R(1) / R(36);
+    if constexpr (FUSED) {
+#pragma clang fp contract(off)
+        const R uu = fma_(N.ux, N.ux, N.uy * N.uy), uT = fma_(N.ux, N.Tx, N.uy * N.Ty);
+        const R oS = om * N.S, hS = R(0.5) * oS, P3 = R(3) * P;
+        const R K0 = fma_(-P3, uT, om * fma_(R(-1.5) * N.S, uu, N.dS));
+        const R Ax = R(3) * N.ux, Ay = R(3) * N.uy, pBx = P3 * N.Tx, pBy = P3 * N.Ty;
+        auto pair = [&](int i, int j, R A, R pB, R w) {
+            const R base = fma_(A, fma_(hS, A, pB), K0), anti = fma_(oS, A, pB);
+            d[i] = fma_(omc, d[i], w * fma_(-hr, D[i], base + anti));
+            d[j] = fma_(omc, d[j], w * fma_(-hr, D[j], base - anti));
+        };
+        d[0] = fma_(omc, d[0], w0 * K0);
+        pair(1, 3, Ax, pBx, w1);
+        pair(2, 4, Ay, pBy, w1);
+        pair(5, 7, Ax + Ay, pBx + pBy, w2);
+        pair(6, 8, Ay - Ax, pBy - pBx, w2);
+        return;
+    }
     const R uu = N.ux * N.ux + N.uy * N.uy;
     const R uT = N.ux * N.Tx + N.uy * N.Ty;
     const R oS = om * N.S, hS = R(0.5) * oS;
     const R K0 = om * (N.dS - R(1.5) * N.S * uu) - R(3) * P * uT;
     const R Ax = R(3) * N.ux, Ay = R(3) * N.uy;
     const R pBx = R(3) * P * N.Tx, pBy = R(3) * P * N.Ty;
-    const R w0 = R(4) / R(9), w1 = R(1) / R(9), w2 = R(1) / R(36);
-    auto less = [&](R v, int k) { return FUSED ? fma_(-hr, D[k], v) : v - de[k]; };
     auto pair = [&](R &di, R &dj, R A, R pB, R w, int i, int j) {
         const R base = K0 + A * (hS * A + pB);
         const R anti = oS * A + pB;
-        di = omc * di + w * less(base + anti, i);
-        dj = omc * dj + w * less(base - anti, j);
+        di = omc * di + w * (base + anti - de[i]);
+        dj = omc * dj + w * (base - anti - de[j]);
     };
     d[0] = omc * d[0] + w0 * K0;
     pair(d[1], d[3], Ax, pBx, w1, 1, 3);
@@ -665,7 +711,7 @@ struct PorNb {
     R D[9];
 };
 
-template <typename R, int W>
+template <typename R, int W, bool FUSED = false>
 __device__ __forceinline__ PorNb<R> porosity_nb(const R (*t)[W], int lyy, int lx, bool wxm,
                                                 bool wxp, bool wym, bool wyp)
 {
@@ -676,8 +722,14 @@ __device__ __forceinline__ PorNb<R> porosity_nb(const R (*t)[W], int lyy, int lx
     const R eSW = t[lyy - 1][lx - 1], eSE = t[lyy - 1][lx + 1];
     const R c1 = R(1) / R(3), c2 = R(1) / R(12);
     P.e0 = e0;
-    P.gex = c1 * (eE - eW) + c2 * ((eNE - eSW) + (eSE - eNW));
-    P.gey = c1 * (eN - eS) + c2 * ((eNE - eSW) + (eNW - eSE));
+    if constexpr (FUSED) {
+#pragma clang fp contract(off)
+        P.gex = fma_(c1, eE - eW, c2 * ((eNE - eSW) + (eSE - eNW)));
+        P.gey = fma_(c1, eN - eS, c2 * ((eNE - eSW) + (eNW - eSE)));
+    } else {
+        P.gex = c1 * (eE - eW) + c2 * ((eNE - eSW) + (eSE - eNW));
+        P.gey = c1 * (eN - eS) + c2 * ((eNE - eSW) + (eNW - eSE));
+    }
     P.D[0] = R(0);
     P.D[1] = wxp ? R(0) : eE - e0;
     P.D[2] = wyp ? R(0) : eN - e0;
@@ -747,11 +799,28 @@ __device__ __forceinline__ void boundary_inflow(R d[9], R e0, bool open_l, bool 
 // w_i dS + S rin[i] for i = 1, 5, 8 into slots 3, 7, 6.  Outlet (x = Lx-1):
 // w_i eps (rho_out P_i(u) - rho0) = w_i eps (dro + rho_out (P_i(u) - 1)) for
 // i = 3, 6, 7 into slots 1, 8, 5, u the node's velocity N of this step.
-template <typename R>
+template <typename R, bool FUSED = false>
 __device__ __forceinline__ void inout_ends(R d[9], const Node<R> &N, R e0, bool open_l,
                                            bool open_r, bool wym, bool wyp, const Phys<R> &ph)
 {
     const R w1 = R(1) / R(9), w2 = R(1) / R(36);
+    if constexpr (FUSED) {
+#pragma clang fp contract(off)
+        if (open_l) {
+            d[3] = fma_(N.S, ph.rin[1], w1 * N.dS);
+            if (!wym) d[7] = fma_(N.S, ph.rin[5], w2 * N.dS);
+            if (!wyp) d[6] = fma_(N.S, ph.rin[8], w2 * N.dS);
+        }
+        if (open_r) {
+            const R uu = R(-1.5) * fma_(N.ux, N.ux, N.uy * N.uy);
+            auto q = [&](R eu) { return fma_(fma_(R(4.5), eu, R(3)), eu, uu); };
+            const R a = e0 * ph.rho_out, b = e0 * ph.dro;
+            d[1] = w1 * fma_(a, q(-N.ux), b);
+            if (!wym) d[8] = w2 * fma_(a, q(N.uy - N.ux), b);
+            if (!wyp) d[5] = w2 * fma_(a, q(-N.ux - N.uy), b);
+        }
+        return;
+    }
     if (open_l) {
         d[3] = w1 * N.dS + N.S * ph.rin[1];
         if (!wym) d[7] = w2 * N.dS + N.S * ph.rin[5];
@@ -797,18 +866,21 @@ __device__ __forceinline__ void update_node_q(R d[9], const PorNb<R> &P, const E
 #pragma unroll
     for (int i = 0; i < 9; i++) de[i] = OUT_SHIFT ? hr * P.D[i] : R(0);
     collide<R, FUSED>(d, N, ph, de, R(0.5) * ph.rho0, P.D);
-    if (ph.inout && (open_l || open_r)) inout_ends<R>(d, N, P.e0, open_l, open_r, wym, wyp, ph);
+    if (ph.inout && (open_l || open_r))
+        inout_ends<R, FUSED>(d, N, P.e0, open_l, open_r, wym, wyp, ph);
 }
 
-template <typename R, int W, bool DIAG, bool IN_FULL = false, bool OUT_SHIFT = true>
+template <typename R, int W, bool DIAG, bool IN_FULL = false, bool OUT_SHIFT = true,
+          bool FUSED = false>
 __device__ __forceinline__ void update_node(R d[9], const R (*t)[W], int lyy, int lx, bool wxm,
                                             bool wxp, bool wym, bool wyp, bool open_l,
                                             bool open_r, const Phys<R> &ph, double *acc,
                                             bool count)
 {
-    const PorNb<R> P = porosity_nb<R, W>(t, lyy, lx, wxm, wxp, wym, wyp);
-    update_node_q<R, DIAG, IN_FULL, OUT_SHIFT>(d, P, eps_terms<R>(P.e0, P.gex, P.gey, ph), wym,
-                                               wyp, open_l, open_r, ph, acc, count);
+    const PorNb<R> P = porosity_nb<R, W, FUSED>(t, lyy, lx, wxm, wxp, wym, wyp);
+    update_node_q<R, DIAG, IN_FULL, OUT_SHIFT, FUSED>(
+        d, P, eps_terms<R, FUSED>(P.e0, P.gex, P.gey, ph), wym, wyp, open_l, open_r, ph, acc,
+        count);
 }
 
 // ---- node update of the FP32 multi-step passes --------------------------------------
@@ -1205,6 +1277,16 @@ __device__ __forceinline__ void gather_vec(R (&d)[9][V], const S *const F[9], in
     left(d[8], raw[8], el[2], !wyp);
 }
 
+// Whether the single steps of a storage are the tiles' arithmetic (update_node_q, FUSED):
+// FP64 and FP32, which tiles and this sweep both take, so that a run has the same bits
+// whichever of them takes a step (recorded or not, alone or in a group).  FP16, which has no
+// tiles, keeps the compiler's own fusing.
+template <typename S>
+constexpr bool fused_steps()
+{
+    return !std::is_same_v<S, _Float16>;
+}
+
 // The fused sweep with V consecutive nodes per lane (a pitch that is a
 // multiple of 64 V); BX: x ends periodic (0), walls (1) or open (2); WY: walls
 // across y; RG: Lx need not be a multiple of V (the last lane of a row may
@@ -1263,8 +1345,9 @@ __device__ __forceinline__ void sweep_vec_tile(const S *__restrict__ fin, S *__r
             const bool wxm = WX && L.x + k == 0;
             const bool wxp = WX && L.x + k == g.Lx - 1;
             const bool ores = BX == 2 && ph.reservoir;
-            update_node<R, W, DIAG>(dk, tile, ly + 1, lane * V + k + 1, wxm, wxp, wym, wyp,
-                                    ores && wxm, ores && wxp, ph, acc, valid && k < L.n);
+            update_node<R, W, DIAG, false, true, fused_steps<S>()>(
+                dk, tile, ly + 1, lane * V + k + 1, wxm, wxp, wym, wyp, ores && wxm, ores && wxp,
+                ph, acc, valid && k < L.n);
 #pragma unroll
             for (int i = 0; i < 9; i++) d[i][k] = dk[i];
         }
@@ -1936,8 +2019,8 @@ __device__ __forceinline__ void tile_steps(const S *__restrict__ fin, S *__restr
     R d[9];
 #pragma unroll
     for (int i = 0; i < 9; i++) d[i] = decode_pop<S, R>(v[i], ph.inv_scale);
-    const PorNb<R> P = porosity_nb<R, 3>(e, 1, 1, wxm, wxp, wym, wyp);
-    const EpsTerms<R> q = eps_terms<R>(P.e0, P.gex, P.gey, ph);
+    const PorNb<R> P = porosity_nb<R, 3, true>(e, 1, 1, wxm, wxp, wym, wyp);
+    const EpsTerms<R> q = eps_terms<R, true>(P.e0, P.gex, P.gey, ph);
     bool ores = BX == 2 && ph.reservoir;
     ph.reservoir = 1;                          // the later steps start from n + 1 >= 1
     const int xm = max(tx - 1, 0), xp = min(tx + 1, TW - 1);
