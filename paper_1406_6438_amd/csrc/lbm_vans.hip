@@ -3391,6 +3391,7 @@ struct lbm_vans_handle {
     int tile_w, tile_ns;    // tile width and most steps per launch of the tile kernel
                             // (choose_tile); tile_ns 0: this lattice does not take it
     bool tile_on;           // lbm_vans_step takes the tile kernel
+    bool tile_one;          // ... also for a launch of one step (one_step_tiles)
     void *scratch;          // device address of the library-held gradient workspace on the
                             // handle's device (lbm_vans_grad_static)
     // Step graphs of small lattices (launch-bound: fewer sweep tiles than twice the
@@ -3930,11 +3931,23 @@ int step_pass(const lbm_vans_handle *h) { return h->p.diag_every > 0 ? 1 : max_p
 //   4.60 (one-step sweep 3.80) / 1.36 (5), 400 x 200 4.69 / 1.76, 640 x 320 4.87 / 2.81, 1024
 //   x 512 6.75 / 5.15, 1024^2 9.19 / 8.76; walls in y alone 512^2 3.77 / 2.94, 1024^2 7.79 /
 //   7.51, 2048^2 26.7 / 31.6.
+// Whether a launch of one step goes on tiles as well, and not to the one-step sweep (the
+// same bits): while both states and the porosity stay in the 256 MB of the last-level cache,
+// where the step is bound by its latency; past that by its bytes, and the sweep's full-width
+// loads are the faster.  Microseconds, sweep / one-step tile: FP64 80 x 80 5.2 / 4.7, 512^2 8.6
+// / 7.8, 1024^2 30 / 26, 1200^2 (219 MB) 44 / 34, 1300^2 (257 MB) 48 / 54, 2048^2 104 / 151;
+// FP32 1024^2 16 / 14, 1800^2 (246 MB) 59 / 48, 2048^2 (319 MB) 54 / 62, 4096^2 207 / 269.
+bool one_step_tiles(long long nodes, int storage)
+{
+    return nodes * 19 * static_cast<long long>(elem_bytes(storage)) <= 256'000'000LL;
+}
+
 void choose_tile(lbm_vans_handle *h, int ncu)
 {
     const lbm_vans_params *p = &h->p;
     h->tile_ns = 0;
     h->tile_on = false;
+    h->tile_one = one_step_tiles(static_cast<long long>(p->Lx) * p->Ly, p->storage);
     if (p->storage == LBM_F16_SHIFTED || p->steps_per_pass != 0 || p->pass_rows != 0 ||
         p->sweep_vec != 0 || h->g.plane * elem_bytes(p->storage) >= (1LL << 31))
         return;
@@ -4108,7 +4121,8 @@ int launch_pass(lbm_vans_handle *h, int m, bool tile = true)
     const void *src = h->buf[h->cur];
     void *dst = h->buf[1 - h->cur];
     int rc;
-    if (h->tile_on && tile) rc = launch_tile(h, src, dst, h->n, m, 0, h->stream);
+    if (h->tile_on && tile && (m > 1 || h->tile_one))
+        rc = launch_tile(h, src, dst, h->n, m, 0, h->stream);
     else if (m >= 2) rc = launch_multi(h, src, dst, m);
     else rc = launch_sweep(h, false);
     if (rc) return rc;
@@ -4655,8 +4669,8 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
             for (int64_t j = 1; j < s1 - s0;) {
                 const void *src = j == 1 ? (const void *)ckpt(c) : (const void *)seg(set, j - 1);
                 int m = 1, rr;
-                if (tiles) {                   // every state of a launch is kept
-                    m = static_cast<int>(std::min<int64_t>(h->tile_ns, s1 - s0 - j));
+                if (tiles) m = static_cast<int>(std::min<int64_t>(h->tile_ns, s1 - s0 - j));
+                if (tiles && (m > 1 || h->tile_one)) {   // every state of a launch is kept
                     rr = launch_tile(h, src, seg(set, j), s0 + j - 1, m, G.pop, rs);
                 } else {
                     rr = launch_sweep_ptrs(h, src, seg(set, j), s0 + j - 1, false, rs);
@@ -5104,10 +5118,20 @@ int batch_next(const lbm_vans_batch *b, int64_t steps)
         std::min<int64_t>(batch_tile_on(b) ? BT_STEPS : batch_max_pass(b), steps));
 }
 
+// Whether a launch of m of them does: a single one, which discards the rings of BT_STEPS
+// steps, only up to half the bytes of the lone rule.  FP64, us per step one at a time, sweep /
+// tiles: 0.15M nodes 8.5 / 8.2, 1.33M 43.7 / 44 to 49, 3.2M 97 / 136, 4.35M 125 / 182; FP32
+// 0.15M 7.2 / 4.9, 1.33M 22 / 21.
+bool batch_tile_takes(const lbm_vans_batch *b, int m)
+{
+    return m > 1 || one_step_tiles(2 * b->nodes, b->storage);
+}
+
 // One batched launch of m steps (batch_next).
 int batch_launch(lbm_vans_batch *b, hipStream_t st, int src, int res_a, int m)
 {
-    if (batch_tile_on(b)) return batch_tile(b, st, src, 1 - src, res_a, m, false);
+    if (batch_tile_on(b) && batch_tile_takes(b, m))
+        return batch_tile(b, st, src, 1 - src, res_a, m, false);
     return m >= 2 ? batch_multi(b, st, src, 1 - src, res_a, m)
                   : batch_sweep(b, st, src, 1 - src, res_a);
 }
@@ -5612,8 +5636,9 @@ int lbm_vans_batch_grad(lbm_vans_batch *b, int32_t objective, int64_t nsteps,
                 const int src = j == 1 ? ckpt_slot(c) : seg_slot(j - 1);
                 const int res = res_on(&b->m[0]->p, s0 + j - 1);
                 int m = 1;
-                if (batch_tile_any(b)) {       // every state of a launch is kept
-                    m = static_cast<int>(std::min<int64_t>(BT_STEPS, s1 - s0 - j));
+                const bool tiles = batch_tile_any(b);
+                if (tiles) m = static_cast<int>(std::min<int64_t>(BT_STEPS, s1 - s0 - j));
+                if (tiles && batch_tile_takes(b, m)) {   // every state of a launch is kept
                     r = batch_tile(b, b->stream, src, seg_slot(j), res, m, true);
                 } else {
                     r = batch_sweep(b, b->stream, src, seg_slot(j), res);
