@@ -348,12 +348,12 @@ typedef struct lbm_vans_batch_config {
                              least as many waves of the batched four-step pass as
                              the GPU holds of it, else 3): with LBM_F32 /
                              LBM_F16_SHIFTED storage the multi-step pass over every
-                             member; vec and grid apply to single steps.  With 0
-                             and pass_rows = 0, LBM_F32_SHIFTED batches of at most
-                             2^21 nodes that do not take the four-step pass, and
-                             with grid = 0 and the widest vec LBM_F64 batches, run
-                             up to three single steps per launch on tiles (the
-                             autotuner does not time these)                        */
+                             member; vec and grid apply to single steps.  Up to
+                             three single steps per launch on tiles are taken by
+                             LBM_F32_SHIFTED batches of at most 2^21 nodes with 3,
+                             or with 0 where that does not lead to the four-step
+                             pass, and pass_rows = 0; and by LBM_F64 batches with
+                             0, grid = 0 and the widest vec                        */
     int32_t pass_rows;    /* rows per chunk of the batched three-step pass, 24 or 28
                              with FP32 storage (0 = automatic: 28 when the whole
                              batch has four times as many waves of 28 rows as the
@@ -387,8 +387,11 @@ int lbm_vans_batch_get_config(const lbm_vans_batch *b, lbm_vans_batch_config *cf
  * of the current state (read only: the state does not change), and, with
  * LBM_F32 / LBM_F16_SHIFTED storage, the two- and three-step passes and, with
  * FP32 storage, the four-step pass (their time per launch divided by 2, 3 and
- * 4; steps_per_pass 2, 3 and 4 in those trials, 1 in the others).  The fastest becomes the configuration (graph_steps kept; the
- * best single-step vec and grid kept when a multi-step pass wins) and is
+ * 4; steps_per_pass 2, 3 and 4 in those trials, 1 in the others).  Where a batch
+ * takes tiles, they are timed as well: LBM_F32_SHIFTED as the trial of three steps
+ * (pass_rows 0), LBM_F64 as one of the automatic configuration (steps_per_pass 0).
+ * The fastest becomes the configuration (graph_steps kept; the best single-step vec
+ * and grid kept when several steps per launch win) and is
  * written to *best (may be NULL); trials
  * (may be NULL if max_trials is 0) receive up to max_trials of the timed
  * shapes and *n_trials (may be NULL) their number.  Synchronises. */

@@ -5092,23 +5092,22 @@ int batch_tile(lbm_vans_batch *b, hipStream_t st, int src, int dst, int res_a, i
     });
 }
 
-// Whether the batch's single steps may go on tiles: automatic steps per launch, and in FP64,
-// which has single steps only, no shape of theirs asked for either.
-bool batch_tile_any(const lbm_vans_batch *b)
-{
-    return b->bt_ok && b->cfg.steps_per_pass == 0 && b->cfg.pass_rows == 0 &&
-           (b->storage != LBM_F64 || (b->cfg.grid == 0 && b->cfg.vec == b->vmax));
-}
-
-// Whether its steps do: FP64, and FP32 batches too small for the four-step pass and of at
-// most BT_NODES nodes.  FP32, us per step of channels of 256 to 1024 columns on three-step
+// Whether the batch's steps go on tiles.  FP64, which has single steps only: with automatic
+// steps per launch and no shape of the sweep asked for.  FP32: with automatic steps per launch
+// or three of them (BT_STEPS) and automatic rows, batches too small for the four-step pass and
+// of at most BT_NODES nodes.  FP32, us per step of channels of 256 to 1024 columns on three-step
 // passes / tiles, by nodes in all: 0.01M 13.5 / 1.9, 0.15M 13.8 / 2.6, 0.98M 14.8 / 8.7, 1.33M
 // 15.3 / 12.1, 2.22M 20.0 / 17.3, 2.70M 20.4 / 21.0.
 constexpr long long BT_NODES = 1LL << 21;
 bool batch_tile_on(const lbm_vans_batch *b)
 {
-    return batch_tile_any(b) && (b->storage == LBM_F64 || batch_max_pass(b) == 1 ||
-                                 (batch_max_pass(b) == 3 && b->nodes <= BT_NODES));
+    const lbm_vans_batch_config &c = b->cfg;
+    if (!b->bt_ok || c.pass_rows != 0) return false;
+    if (b->storage == LBM_F64)
+        return c.steps_per_pass == 0 && c.grid == 0 && c.vec == b->vmax;
+    if (c.steps_per_pass != 0 && c.steps_per_pass != BT_STEPS) return false;
+    const int m = batch_max_pass(b);
+    return m == 1 || (m == 3 && b->nodes <= BT_NODES);
 }
 
 // Steps the next batched launch takes of `steps` that remain.
@@ -5453,24 +5452,43 @@ int lbm_vans_batch_tune(lbm_vans_batch *b, int32_t reps, lbm_vans_batch_config *
             if (b->cfg.us_per_step < top.us_per_step) top = b->cfg;
         }
     }
-    // the multi-step passes (independent of vec and grid; the single-step shape
-    // found so far is kept for the steps they leave over), timed per step
+    // the launches of several steps (independent of vec and grid; the single-step shape
+    // found so far is kept for the steps they leave over), timed per step: the multi-step
+    // passes, three steps on tiles where that configuration takes them, and the automatic
+    // configuration where it takes tiles and none of these does (FP64, or members too short
+    // for the multi-step passes)
     const lbm_vans_batch_config single = top;
-    const int ns_max = b->multi4_ok ? 4 : 3;
-    for (int ns = 2; ns <= ns_max && b->storage != LBM_F64 && b->nwaves[0] > 0 && b->multi_ok;
-         ns++) {
-        rc = batch_multi(b, b->stream, src, dst, res, ns);
+    const bool multi = b->storage != LBM_F64 && b->nwaves[0] > 0 && b->multi_ok;
+    for (int ns = 0; ns <= (b->multi4_ok ? 4 : 3); ns++) {
+        lbm_vans_batch_config pc = single;
+        pc.steps_per_pass = ns;
+        if (ns == 0) {
+            pc.vec = b->vmax;
+            pc.grid = 0;
+        }
+        if (ns == 0 || ns == BT_STEPS) {
+            pc.pass_rows = 0;
+            b->cfg = pc;
+            if (!batch_tile_on(b)) pc.pass_rows = keep.pass_rows;
+        }
+        b->cfg = pc;
+        const bool tiles = batch_tile_on(b);
+        if (ns == 0 ? !tiles || multi : ns == 1 || !multi) continue;
+        const int m = tiles ? BT_STEPS : ns;
+        auto launch = [&] {
+            return tiles ? batch_tile(b, b->stream, src, dst, res, m, false)
+                         : batch_multi(b, b->stream, src, dst, res, m);
+        };
+        rc = launch();
         if (rc) return rc;
         HIP_TRY(hipEventRecord(b->ev[0], b->stream));
-        for (int r = 0; r < reps && !rc; r++) rc = batch_multi(b, b->stream, src, dst, res, ns);
+        for (int r = 0; r < reps && !rc; r++) rc = launch();
         if (rc) return rc;
         HIP_TRY(hipEventRecord(b->ev[1], b->stream));
         HIP_TRY(hipEventSynchronize(b->ev[1]));
         float ms = 0.0f;
         HIP_TRY(hipEventElapsedTime(&ms, b->ev[0], b->ev[1]));
-        lbm_vans_batch_config pc = single;
-        pc.steps_per_pass = ns;
-        pc.us_per_step = 1000.0 * ms / (static_cast<double>(ns) * reps);
+        pc.us_per_step = 1000.0 * ms / (static_cast<double>(m) * reps);
         if (nt < max_trials) trials[nt] = pc;
         nt++;
         if (pc.us_per_step < top.us_per_step) top = pc;
@@ -5636,7 +5654,8 @@ int lbm_vans_batch_grad(lbm_vans_batch *b, int32_t objective, int64_t nsteps,
                 const int src = j == 1 ? ckpt_slot(c) : seg_slot(j - 1);
                 const int res = res_on(&b->m[0]->p, s0 + j - 1);
                 int m = 1;
-                const bool tiles = batch_tile_any(b);
+                // whatever launches the steps take: the bits are those of the sweep
+                const bool tiles = b->bt_ok;
                 if (tiles) m = static_cast<int>(std::min<int64_t>(BT_STEPS, s1 - s0 - j));
                 if (tiles && batch_tile_takes(b, m)) {   // every state of a launch is kept
                     r = batch_tile(b, b->stream, src, seg_slot(j), res, m, true);

@@ -476,7 +476,9 @@ class Batch:
                   pass_rows: int = 0):
         """steps_per_pass: most steps per launch (0 = automatic: 4 or 3 with FP32
         storage, 3 with FP16; 1, 2, 3, or 4 with FP32); pass_rows: rows per chunk of the
-        three-step pass (0 = automatic; 24 or 28 with FP32 storage)."""
+        three-step pass (0 = automatic; 24 or 28 with FP32 storage).  Small FP32 batches
+        with 0 or 3 steps and automatic rows, and FP64 ones in their automatic
+        configuration, take single steps on tiles."""
         lbm_vans_batch_configure(self.b, vec, grid, graph_steps, steps_per_pass, pass_rows)
 
     @property

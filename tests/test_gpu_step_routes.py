@@ -3,7 +3,8 @@ chooses between (all of them give the same bits or results within rounding).
 
 Each comparison times both sides in turn on the same lattice, best of several, and allows 20%:
 the routes it tells apart differ by 40% and more (FP64 2048^2, one step: one-step sweep 104 us,
-one-step tile 151); 6% where a step with its record is timed too (4096^2 FP32: 475 / 521).
+one-step tile 151; a tuned FP32 batch of 0.15M nodes: 5.3 us a step on sweeps, 2.5 on tiles);
+6% where a step with its record is timed too (4096^2 FP32: 475 / 521).
 """
 import dataclasses
 
@@ -94,3 +95,38 @@ def test_batched_single_steps_are_not_slower_than_the_sweep():
         sweep.close()
         for s in sv[0] + sv[1]:
             s.close()
+
+
+def _members(storage, sizes):
+    from paper_1406_6438_amd import lbm
+    return [lbm.Solver(Spec(Lx=Lx, Ly=Lx // 2, tau=0.8, d_p=20.0, u0=(0.02, 0.0), walls_y=True,
+                            inout=True, u_in=0.02, storage=storage).gpu(),
+                       _eps(Lx, Lx // 2, storage, Lx)) for Lx in sizes]
+
+
+@pytest.mark.parametrize("storage, sizes", [("f32", (129, 250, 470)), ("f32", (900, 1010)),
+                                            ("f64", (129, 250, 470)), ("f64", (900, 1010)),
+                                            ("f64", (9, 12)), ("f32", (2048, 2048, 1500))])
+def test_tuned_batch_is_not_slower_than_an_untuned_one(storage, sizes):
+    """The tuner's pick against the automatic configuration: steps (several graphs of them)
+    and the gradient, whose recomputed states do not depend on the pick; and a batch
+    configured with what the tuner returned runs what the tuner timed."""
+    from paper_1406_6438_amd import lbm
+    sv = [_members(storage, sizes) for _ in range(3)]
+    tuned, auto, copied = (lbm.Batch(s) for s in sv)
+    for b in (tuned, auto, copied):
+        b.step(1)
+    best, trials = tuned.tune(reps=10)
+    assert best["us_per_step"] == min(t["us_per_step"] for t in trials)
+    copied.configure(best["vec"], best["grid"], best["graph_steps"], best["steps_per_pass"],
+                     best["pass_rows"])
+    say(f"[routes] tuned {storage} {sizes}: {best}")
+    _compare(f"tuned {storage} {sizes}", lambda: tuned.step(96), lambda: auto.step(96), 2)
+    _compare(f"configured as tuned {storage} {sizes}", lambda: copied.step(96),
+             lambda: tuned.step(96), 2)
+    _compare(f"gradient of the tuned {storage} {sizes}", lambda: tuned.grad(60, 20),
+             lambda: auto.grad(60, 20), 1, rounds=5)
+    for b in (tuned, auto, copied):
+        b.close()
+    for s in sum(sv, []):
+        s.close()
