@@ -259,14 +259,16 @@ def speed_error(gpu, res) -> float:
 def crop_sample(w, lbm, steps: int, plan):
     """The GPU run of the top-left 512^2 crop of the workload's porosity, run periodic
     in the launch plan of the timed run (plan = steps per pass, rows per chunk of the
-    multi-step pass), and the matching oracle job."""
+    multi-step pass; None: single steps on tiles), and the matching oracle job."""
     import dataclasses
     from paper_1406_6438_amd import workloads as W
     n = W.CROP
     eps = cast_eps(W.crop_porosity(w, n), w.storage)
-    p = dataclasses.replace(lbm_params(w, lbm, n, n), steps_per_pass=plan[0],
-                            pass_rows=plan[1])
+    p = lbm_params(w, lbm, n, n)
+    if plan is not None:
+        p = dataclasses.replace(p, steps_per_pass=plan[0], pass_rows=plan[1])
     s = lbm.Solver(p, eps)
+    assert plan is not None or s.tile_plan
     s.step(steps)
     m = s.moments(want_diag=False)
     gpu = (m["ux"].double().cpu().numpy(), m["uy"].double().cpu().numpy())
@@ -284,14 +286,16 @@ def time_sweep(w, lbm, torch, steps: int, warmup: int, single_steps: int = 0, re
     seconds of every repetition and their median, the mean duration of the launches
     that take the plan's full steps per pass (the dominant kernel), the final
     diagnostics record, the porosity, the seconds per step when every step is its own
-    launch (k_sweep_vec; None without single_steps) and the launch plan (most steps per
-    pass, rows per chunk of the multi-step pass)."""
+    launch (k_sweep_vec; None without single_steps), the launch plan (most steps per
+    pass, rows per chunk of the multi-step pass; None for single steps on tiles), the
+    steps per launch and the kernel that takes them."""
     import statistics
     eps = w.porosity()
     s = lbm.Solver(lbm_params(w, lbm), cast_eps(eps, w.storage))
-    plan = s.pass_plan
-    spl = plan[0]
-    log(f"[bench] {w.name}: warmup {warmup} steps; plan {plan}")
+    plan = None if s.tile_plan else s.pass_plan
+    spl = s.tile_plan or plan[0]
+    kernel = "k_sweep_tile" if s.tile_plan else MULTI_KERNEL[spl]
+    log(f"[bench] {w.name}: warmup {warmup} steps; {spl} steps per launch of {kernel}, plan {plan}")
     s.step(warmup)
     torch.cuda.synchronize()
     Ev = lambda: torch.cuda.Event(enable_timing=True)  # noqa: E731
@@ -334,7 +338,8 @@ def time_sweep(w, lbm, torch, steps: int, warmup: int, single_steps: int = 0, re
         f"steps, {launch * 1e6:.2f} us each"
         + (f"; one step per launch: {single * 1e6:.1f} us/step" if single else ""))
     return {"median_s": med, "rep_s": rep_s, "launch_s": launch, "launches": len(launch_s),
-            "diag": diag, "eps": eps, "single_s": single, "plan": plan}
+            "diag": diag, "eps": eps, "single_s": single, "plan": plan, "spl": spl,
+            "kernel": kernel}
 
 
 def adjoint_params(lbm, w, Lx=None, Ly=None):
@@ -456,10 +461,11 @@ def ensemble_leg(lbm, torch, no_accuracy: bool, steps: int, warmup: int, grad: b
     t_plain = timed(steps)
     b.configure(best["vec"], best["grid"], best["graph_steps"], best["steps_per_pass"],
                 best["pass_rows"])
-    spl, rows = b.pass_plan
+    spl, rows = (b.tile_plan, 0) if b.tile_plan else b.pass_plan
+    kernel = "k_batch_tile" if b.tile_plan else BATCH_KERNEL[spl]
     bpn = algorithmic_bytes_per_node("f32")
     # the graphs replay launches of spl steps: the time of one is the time per step x spl
-    roof = roofline(BATCH_KERNEL[spl], "ensemble64_f32" if len(members) == 64 else "-", bpn,
+    roof = roofline(kernel, "ensemble64_f32" if len(members) == 64 else "-", bpn,
                     cells, t_graph / steps * spl, spl, rows)
     roof["launch_time"] = "time per step of the graph replays x steps per launch"
     out = {"workload": f"ensemble_{len(members)}_channels_f32", "members": len(members),
@@ -603,8 +609,9 @@ def main():
     cells = w.Lx * w.Ly
     mlups = cells * args.steps / gpu_s / 1e6
     bpn = algorithmic_bytes_per_node(w.storage)
-    spl = plan[0]                       # steps per launch of the timed run
-    roof = roofline(MULTI_KERNEL[spl], args.workload, bpn, cells, ts["launch_s"], spl, plan[1])
+    spl = ts["spl"]                     # steps per launch of the timed run
+    roof = roofline(ts["kernel"], args.workload, bpn, cells, ts["launch_s"], spl,
+                    plan[1] if plan else 0)
     copy_bw = copy_bandwidth_gbps(torch)
     roof["device_copy_GBps"] = round(copy_bw, 1)
     log(f"[bench] {mlups:.1f} MLUPS; {roof['kernel']} {roof['launch_us']} us per launch, "
@@ -616,7 +623,8 @@ def main():
     acc = None
     if want_acc and w.storage != "f64":
         gpu, job = crop_sample(w, lbm, w.steps, plan)
-        acc = {"kernel": roof["kernel"], "steps_per_pass": plan[0], "pass_rows": plan[1]}
+        acc = {"kernel": roof["kernel"], "steps_per_pass": plan[0] if plan else 1,
+               "pass_rows": plan[1] if plan else 0}
         samples.append((acc, gpu, job, f"top-left 512x512 crop of the porosity field, periodic, "
                                        f"{w.steps} steps in the timed run's launch plan"))
 

@@ -4358,9 +4358,17 @@ int lbm_vans_pass_plan(const lbm_vans_handle *h, int32_t *steps_per_pass, int32_
 {
     if (!h) return fail(LBM_VANS_EINVAL, "handle is NULL");
     const bool multi = h->p.storage != LBM_F64 && multi_fits(h->g);
-    const int m = max_pass(h);
+    const int m = step_pass(h);
     if (steps_per_pass) *steps_per_pass = m;
     if (pass_rows) *pass_rows = multi ? (m == 4 ? tb_rows<float, 4>() : h->rows3) : 0;
+    return LBM_VANS_OK;
+}
+
+int lbm_vans_tile_plan(const lbm_vans_handle *h, int32_t *steps)
+{
+    if (!h) return fail(LBM_VANS_EINVAL, "handle is NULL");
+    if (!steps) return fail(LBM_VANS_EINVAL, "steps is NULL");
+    *steps = h->tile_on ? h->tile_ns : 0;
     return LBM_VANS_OK;
 }
 
@@ -5398,6 +5406,14 @@ int lbm_vans_batch_pass_plan(const lbm_vans_batch *b, int32_t *steps_per_pass,
                      : m == 4 ? tb_rows<float, 4>()
                      : batch_tall(b) ? LBM_VANS_TB3_TALL32
                                      : tb_rows<float, 3>();
+    return LBM_VANS_OK;
+}
+
+int lbm_vans_batch_tile_plan(const lbm_vans_batch *b, int32_t *steps)
+{
+    if (!b) return fail(LBM_VANS_EINVAL, "batch is NULL");
+    if (!steps) return fail(LBM_VANS_EINVAL, "steps is NULL");
+    *steps = batch_tile_on(b) ? BT_STEPS : 0;
     return LBM_VANS_OK;
 }
 

@@ -33,7 +33,8 @@ ABI_VERSION = 9
 
 # Every symbol include/lbm_vans.h declares.
 SYMBOLS = ("lbm_vans_work_bytes", "lbm_vans_init", "lbm_vans_step", "lbm_vans_step_count",
-           "lbm_vans_pass_plan", "lbm_vans_batch_pass_plan", "lbm_vans_moments", "lbm_vans_get_state", "lbm_vans_set_state",
+           "lbm_vans_pass_plan", "lbm_vans_batch_pass_plan", "lbm_vans_tile_plan",
+           "lbm_vans_batch_tile_plan", "lbm_vans_moments", "lbm_vans_get_state", "lbm_vans_set_state",
            "lbm_vans_diag_read", "lbm_vans_grad_work_bytes", "lbm_vans_grad",
            "lbm_vans_grad_static", "lbm_vans_objective",
            "lbm_vans_destroy", "lbm_vans_batch_work_bytes", "lbm_vans_batch_create",
@@ -139,6 +140,8 @@ def load(path: str = LIB_PATH):
     i32p = ctypes.POINTER(i32)
     L.lbm_vans_pass_plan.argtypes = [vp, i32p, i32p]
     L.lbm_vans_batch_pass_plan.argtypes = [vp, i32p, i32p]
+    L.lbm_vans_tile_plan.argtypes = [vp, i32p]
+    L.lbm_vans_batch_tile_plan.argtypes = [vp, i32p]
     L.lbm_vans_moments.argtypes = [vp, vp, vp, vp, vp, dp]
     L.lbm_vans_get_state.argtypes = [vp, vp]
     L.lbm_vans_set_state.argtypes = [vp, vp]
@@ -170,8 +173,8 @@ def load(path: str = LIB_PATH):
     L.lbm_vans_abi_version.argtypes = []
     for n in ("lbm_vans_init", "lbm_vans_step", "lbm_vans_moments", "lbm_vans_get_state",
               "lbm_vans_set_state", "lbm_vans_diag_read", "lbm_vans_grad",
-              "lbm_vans_grad_static", "lbm_vans_objective",
-              "lbm_vans_batch_create", "lbm_vans_batch_configure", "lbm_vans_batch_get_config",
+              "lbm_vans_grad_static", "lbm_vans_objective", "lbm_vans_tile_plan",
+              "lbm_vans_batch_tile_plan", "lbm_vans_batch_create", "lbm_vans_batch_configure", "lbm_vans_batch_get_config",
               "lbm_vans_batch_tune", "lbm_vans_batch_step", "lbm_vans_batch_grad",
               "lbm_vans_abi_version"):
         getattr(L, n).restype = ctypes.c_int
@@ -320,6 +323,21 @@ def lbm_vans_batch_pass_plan(b) -> tuple:
     return spp.value, rows.value
 
 
+def lbm_vans_tile_plan(h) -> int:
+    """Most single steps one launch of lbm_vans_step takes on tiles (0: the passes of
+    lbm_vans_pass_plan run)."""
+    n = ctypes.c_int32()
+    _check(load().lbm_vans_tile_plan(h, ctypes.byref(n)))
+    return n.value
+
+
+def lbm_vans_batch_tile_plan(b) -> int:
+    """lbm_vans_tile_plan for batched launches under the current configuration."""
+    n = ctypes.c_int32()
+    _check(load().lbm_vans_batch_tile_plan(b, ctypes.byref(n)))
+    return n.value
+
+
 def lbm_vans_batch_get_config(b) -> dict:
     c = LbmVansBatchConfig()
     _check(load().lbm_vans_batch_get_config(b, ctypes.byref(c)))
@@ -397,8 +415,14 @@ class Solver:
 
     @property
     def pass_plan(self) -> tuple:
-        """(most steps per pass, rows per chunk of the three-step pass or 0)."""
+        """(most steps per pass, rows per chunk of the three-step pass or 0): what step()
+        follows where tile_plan is 0."""
         return lbm_vans_pass_plan(self.h)
+
+    @property
+    def tile_plan(self) -> int:
+        """Most single steps per launch on tiles, or 0 where step() follows pass_plan."""
+        return lbm_vans_tile_plan(self.h)
 
     def moments(self, want_diag: bool = True):
         """dict of eps_rho, rho, ux, uy tensors [Ly, Lx] and the diagnostics record."""
@@ -487,8 +511,14 @@ class Batch:
 
     @property
     def pass_plan(self) -> tuple:
-        """(most steps per launch, rows per chunk of the three-step pass or 0)."""
+        """(most steps per launch, rows per chunk of the three-step pass or 0): what step()
+        follows where tile_plan is 0."""
         return lbm_vans_batch_pass_plan(self.b)
+
+    @property
+    def tile_plan(self) -> int:
+        """Most single steps per launch on tiles, or 0 where step() follows pass_plan."""
+        return lbm_vans_batch_tile_plan(self.b)
 
     def tune(self, reps: int = 5):
         """Autotune the launch shape; returns (best, all trials) as dicts."""
