@@ -282,7 +282,8 @@ size_t lbm_vans_grad_work_bytes(const lbm_vans_params *p, int32_t objective, int
  * dJdeps(x) = dJ/deps(x), the exact derivative of the discrete map (up to
  * rounding), computed by the reverse (adjoint) sweep: a forward pass keeping
  * a checkpoint every ckpt_every steps (up to three steps per pass in between, as
- * in lbm_vans_step, when params.steps_per_pass allows it), then, segment by segment
+ * in lbm_vans_step, when params.steps_per_pass allows it, whatever
+ * params.diag_every is: a gradient records nothing), then, segment by segment
  * from the last, the states recomputed one step at a time from the
  * checkpoint (on a second stream of the handle, one segment ahead) and the
  * adjoint stepped back through them.  Porosity enters

@@ -3391,6 +3391,7 @@ struct lbm_vans_handle {
     int tile_w, tile_ns;    // tile width and most steps per launch of the tile kernel
                             // (choose_tile); tile_ns 0: this lattice does not take it
     bool tile_on;           // lbm_vans_step takes the tile kernel
+    bool tile_fwd;          // ... or would if it recorded nothing (the gradient's forward)
     bool tile_one;          // ... also for a launch of one step (one_step_tiles)
     void *scratch;          // device address of the library-held gradient workspace on the
                             // handle's device (lbm_vans_grad_static)
@@ -3946,7 +3947,7 @@ void choose_tile(lbm_vans_handle *h, int ncu)
 {
     const lbm_vans_params *p = &h->p;
     h->tile_ns = 0;
-    h->tile_on = false;
+    h->tile_on = h->tile_fwd = false;
     h->tile_one = one_step_tiles(static_cast<long long>(p->Lx) * p->Ly, p->storage);
     if (p->storage == LBM_F16_SHIFTED || p->steps_per_pass != 0 || p->pass_rows != 0 ||
         p->sweep_vec != 0 || h->g.plane * elem_bytes(p->storage) >= (1LL << 31))
@@ -3955,9 +3956,13 @@ void choose_tile(lbm_vans_handle *h, int ncu)
         const int ow = w - 2 * (ns - 1), oh = TILE_H - 2 * (ns - 1);
         return static_cast<long long>((p->Lx + ow - 1) / ow) * ((p->Ly + oh - 1) / oh);
     };
+    auto takes = [&](int pass) {
+        return pass == 1 || (pass == 3 && h->rows3 <= LBM_VANS_TB3_SHORT32 &&
+                             static_cast<long long>(p->Lx) * p->Ly <= (1LL << 20));
+    };
     const int m = step_pass(h);
-    h->tile_on = m == 1 || (m == 3 && h->rows3 <= LBM_VANS_TB3_SHORT32 &&
-                            static_cast<long long>(p->Lx) * p->Ly <= (1LL << 20));
+    h->tile_on = takes(m);
+    h->tile_fwd = takes(max_pass(h));
     h->tile_w = 32;
     h->tile_ns = 3;
     if (m == 1 && tiles(16, 6) <= ncu) {
@@ -4092,9 +4097,8 @@ int launch_tile(lbm_vans_handle *h, const void *src, void *dst, int64_t n, int n
     });
 }
 
-// Whether the gradient's forward and recomputed states come from the tile kernel (in FP64
-// both or neither: the same bits for any checkpoint interval), and in FP64 its reverse steps
-// from the reverse tiles.  Not for FP64 lattices above 2^19 nodes, where the recompute and
+// Whether the gradient's recomputed states, and its forward where the handle's steps do
+// (tile_fwd), come from the tile kernel, and in FP64 its reverse steps from the reverse tiles.  Not for FP64 lattices above 2^19 nodes, where the recompute and
 // the reverse step beside it on the other stream contend for the FP64 units and the rings'
 // arithmetic costs more than the bytes saved (us per step of the whole gradient, one-step
 // launches and rows / tiles: 512 x 300 29.9 / 20.8, 1024 x 512 60.3 / 57.2, 1024^2 109.6 /
@@ -4106,22 +4110,21 @@ bool grad_tiles(const lbm_vans_handle *h)
                           static_cast<long long>(h->p.Lx) * h->p.Ly <= (1LL << 19));
 }
 
-// Steps the next launch takes of `steps` that remain (no diagnostics among them); tile: the
-// tile kernel may take them.
-int next_pass(const lbm_vans_handle *h, int64_t steps, bool tile = true)
+// Steps the next launch of lbm_vans_step takes of `steps` that remain (no diagnostics among
+// them).
+int next_pass(const lbm_vans_handle *h, int64_t steps)
 {
-    const int m = step_pass(h);
-    return static_cast<int>(std::min<int64_t>(h->tile_on && tile ? h->tile_ns : m, steps));
+    return static_cast<int>(std::min<int64_t>(h->tile_on ? h->tile_ns : step_pass(h), steps));
 }
 
-// One launch of m steps (next_pass) from the handle's current state into its other buffer;
-// the handle's state slot and step count advance.
-int launch_pass(lbm_vans_handle *h, int m, bool tile = true)
+// One launch of m steps from the handle's current state into its other buffer, on tiles
+// (tile) or as a pass; the handle's state slot and step count advance.
+int launch_pass(lbm_vans_handle *h, int m, bool tile)
 {
     const void *src = h->buf[h->cur];
     void *dst = h->buf[1 - h->cur];
     int rc;
-    if (h->tile_on && tile && (m > 1 || h->tile_one))
+    if (tile && (m > 1 || h->tile_one))
         rc = launch_tile(h, src, dst, h->n, m, 0, h->stream);
     else if (m >= 2) rc = launch_multi(h, src, dst, m);
     else rc = launch_sweep(h, false);
@@ -4266,7 +4269,7 @@ int plain_steps(lbm_vans_handle *h, int64_t steps)
 {
     for (int64_t k = 0; k < steps;) {
         const int m = next_pass(h, steps - k);
-        const int rc = launch_pass(h, m);
+        const int rc = launch_pass(h, m, h->tile_on);
         if (rc) return rc;
         k += m;
     }
@@ -4334,7 +4337,7 @@ int lbm_vans_step(lbm_vans_handle *h, int64_t nsteps)
             const int64_t left = every > 0 ? std::min<int64_t>(nsteps, every - h->n % every)
                                            : nsteps;
             const int m = next_pass(h, left);
-            const int rc = launch_pass(h, m);
+            const int rc = launch_pass(h, m, h->tile_on);
             if (rc) return rc;
             nsteps -= m;
             continue;
@@ -4611,14 +4614,17 @@ int grad_run(lbm_vans_handle *h, int32_t objective, int64_t nsteps, int32_t ckpt
         if (r) return r;
         h->cur = 0;
         h->n = 0;
-        const bool tiles = grad_tiles(h);
+        // as the steps would go if they recorded nothing: J and the gradient do not depend on
+        // diag_every
+        const bool tiles = grad_tiles(h), fwd = tiles && h->tile_fwd;
         for (int64_t s0 = 0; s0 < nsteps || s0 == 0; s0 += K) {
             HIP_TRY(hipMemcpyAsync(ckpt(s0 / K), h->buf[h->cur], G.pop, hipMemcpyDeviceToDevice,
                                    h->stream));
             // only the checkpoints are kept: several steps per launch in between
             for (int64_t k = 0; k < K && s0 + k < nsteps;) {
-                const int m = next_pass(h, std::min<int64_t>(K - k, nsteps - s0 - k), tiles);
-                r = launch_pass(h, m, tiles);
+                const int m = static_cast<int>(
+                    std::min<int64_t>({fwd ? h->tile_ns : max_pass(h), K - k, nsteps - s0 - k}));
+                r = launch_pass(h, m, fwd);
                 if (r) return r;
                 k += m;
             }

@@ -119,6 +119,24 @@ def test_gradient_forward_ends_in_the_state_of_the_steps(storage):
     assert torch.equal(out[2][1], out[1][1])   # the same launches, recorded or not
 
 
+@pytest.mark.parametrize("storage, L", [("f16", (2048, 1024)), ("f32", (2048, 1024)),
+                                        ("f32", (512, 300)), ("f64", (97, 64))])
+def test_gradient_does_not_depend_on_recording(storage, L):
+    """A gradient records nothing, so its passes (several steps each for the larger lattices)
+    are those of a handle without diagnostics: the same bits of J, gradient and last state."""
+    from paper_1406_6438_amd import lbm
+    spec, eps = _case(storage, "inout", "ergun", *L, 0.8)
+    out = []
+    for every in (0, 5):
+        s = lbm.Solver(dataclasses.replace(spec, diag_every=every).gpu(), eps)
+        J, g = s.grad(12, 6)
+        out.append((J, g, s.get_state()))
+        s.close()
+    say(f"[gradient {storage} {L}] J {out[0][0]!r} {out[1][0]!r}")
+    assert out[0][0] == out[1][0]
+    assert torch.equal(out[0][1], out[1][1]) and torch.equal(out[0][2], out[1][2])
+
+
 @pytest.mark.parametrize("storage", ["f64", "f32"])
 def test_records_do_not_depend_on_the_launches(storage):
     """The recorded states are the same bits whatever takes the steps between them, and one
