@@ -279,10 +279,9 @@ struct Phys {
     R ca, cb;       // Ergun drag prefactors (0 under the constant law; see drag_coeffs)
     R ka, kb;       // constant-K drag prefactors (0 under the Ergun law)
     R scale, inv_scale;  // FP16 storage scale 2^s and 2^-s (1 otherwise)
-    // Constants of the FP32 multi-step passes' node update (collide_w): omega (om, rounded
-    // so that its companions are exact), 1 - omega and half of it, omega / 2, 2 - omega,
-    // G / 2 and rho0 / 2.
-    R om, omc, omc2, omh, P2, Ghx, Ghy, c2;
+    // Constants of the FP32 multi-step passes' node update (collide_w): 1 - omega and half of
+    // it, omega / 2 and rho0 / 2.
+    R omc, omc2, omh, c2;
     // Open x ends: a population entering across x = 0 (x = Lx-1) is the
     // equilibrium of a reservoir with the node's porosity, density rho_in
     // (rho_out) and velocity (u_in, 0) ((u_out, 0)); as a deviation from the
@@ -886,20 +885,25 @@ __device__ __forceinline__ void update_node(R d[9], const R (*t)[W], int lyy, in
 // ---- node update of the FP32 multi-step passes --------------------------------------
 // Their steps carry weighted deviations g_i = d_i / w_i, the same scale in every direction,
 // and update opposite directions i, j as a pair, on their sum and difference.  With
-// omega = 1/tau, P = 1 - omega/2 and h = omega S/2 u + P T the collision (see collide) is
+// omega = 1/tau and h = omega S/2 u + (1 - omega/2) T the collision (see collide) is
 //   g*_i   = (1 - omega) g_i + base_i + anti_i,
 //   base_i = K0 + 9 (e_i.u) (e_i.h)                  even under e_i -> -e_i,
 //   anti_i = 3 e_i.(omega S/2 u + h)                 odd,
 //   K0     = omega (dS - 3/2 S u.u) - 3 P u.T = omega dS - 3 u.h:
 // no weight multiplies a direction, u.u and u.T never appear, and the even terms of all
-// directions come from u_x h_x, u_y h_y and the cross term u_x h_y + u_y h_x.  T enters as
-// T = 2 (q - drag/2 u) with q = (Q + G)/2, which the velocity needs anyway.
+// directions come from u_x h_x, u_y h_y and the cross term u_x h_y + u_y h_x.  The velocity
+// is formed of doubled terms, q = Q + G and V = 2 m + q, so that T = q - drag u takes the same
+// q, and h = T + omega/2 (S u - T): the factor 1 - omega/2, which FP32 does not hold for every
+// omega, never appears.
 // The constants are chosen so that a fluid at rest in a porosity gradient stays at rest to
-// rounding: the link shift and q share the factor 1/72, and 1 - omega and 2 - omega are
-// exact companions of omega (a mismatch of 1e-7 between them acts as a constant force:
+// rounding: the link shift and q share the factor 1/36, and omega enters all terms as the
+// same value (a mismatch of 1e-7 between two of its companions acts as a constant force:
 // with the weights folded into omega / 36 and P / 36 the velocity error against 64 bits
-// after 100 steps was 4..12e-6; as written it is 1.6..3.8e-6, with the one-step sweep's
-// form of the update in these passes 1.8..4.9e-6).
+// after 100 steps was 4..12e-6 where this form's was 1.6..3.8e-6).  Velocity error of a
+// 400 x 300 periodic box after 100 steps at tau 0.6 / 0.7 / 1.5 / 1.97, in 1e-7: omega
+// rounded to a multiple of 2^-23 beside an exact 2 - omega, which takes omega's last bit for
+// tau in (1, 2], 11.0 / 8.8 / 4.6 / 4.1; as written 10.2 / 8.2 / 2.9 / 3.9; one-step sweep
+// 12.8 / 11.4 / 4.6 / 4.2.
 // The passes issue 13% fewer vector instructions for it (4096^2 box, four steps: 1.65e8 ->
 // 1.43e8 wave instructions a launch, 91% of the SIMDs' cycles busy) and the four-step pass
 // then runs at the rate of its memory pattern (a copy kernel with the same strips and halo
@@ -908,10 +912,10 @@ __device__ __forceinline__ void update_node(R d[9], const R (*t)[W], int lyy, in
 // closed 1003 x 751 box 88 / 93 (6 rows 93 / 103), 1024^2 with walls in y 115 / 127,
 // 16-member ensemble 160 / 168.
 
-// The porosity-only terms of a node's update (the same at every step): 1/eps, a sixth of
-// the lattice gradient of eps, and half of the drag coefficients a and b.
+// The porosity-only terms of a node's update (the same at every step): 1/eps, a third of
+// the lattice gradient of eps, and the drag coefficients a and b.
 struct NodeEps {
-    float ie, gx, gy, ha, hb;
+    float ie, gx, gy, a, b;
 };
 
 // The porosity around one node: eps(x) and the differences D[i] = eps(x + e_i) - eps(x),
@@ -944,14 +948,11 @@ __device__ __forceinline__ NodeEps node_eps(const float (&t)[3][3], const Phys<f
 {
     const float e0 = t[1][1];
     const float d1 = t[2][2] - t[0][0], d2 = t[0][2] - t[2][0];
-    float a, b;
     NodeEps q;
     q.ie = rcp(e0);
-    q.gx = (1.0f / 72.0f) * fma_(4.0f, t[1][2] - t[1][0], d1 + d2);
-    q.gy = (1.0f / 72.0f) * fma_(4.0f, t[2][1] - t[0][1], d1 - d2);
-    drag_coeffs(ph, e0, q.ie, a, b);
-    q.ha = 0.5f * a;
-    q.hb = 0.5f * b;
+    q.gx = (1.0f / 36.0f) * fma_(4.0f, t[1][2] - t[1][0], d1 + d2);
+    q.gy = (1.0f / 36.0f) * fma_(4.0f, t[2][1] - t[0][1], d1 - d2);
+    drag_coeffs(ph, e0, q.ie, q.a, q.b);
     return q;
 }
 
@@ -1019,27 +1020,27 @@ __device__ __forceinline__ void collide_w(float g[9], const LinkEps &P, const No
                                           const Phys<float> &ph)
 {
 #pragma clang fp contract(off)
-    const float w = 1.0f / 36.0f;
+    const float w = 1.0f / 36.0f, wv = 1.0f / 18.0f;
     const float s13 = g[1] + g[3], a13 = g[1] - g[3], s24 = g[2] + g[4], a24 = g[2] - g[4];
     const float s57 = g[5] + g[7], a57 = g[5] - g[7], s68 = g[6] + g[8], a68 = g[6] - g[8];
     const float dS = w * fma_(16.0f, g[0], fma_(4.0f, s13 + s24, s57 + s68));
     const float mx = fma_(4.0f, a13, a57 - a68), my = fma_(4.0f, a24, a57 + a68);   // 36 m
     const float S = fma_(P.e0, ph.rho0, dS);
     const float rho = S * q.ie;
-    const float qx = fma_(rho, q.gx, ph.Ghx), qy = fma_(rho, q.gy, ph.Ghy);
-    const float Vx = fma_(w, mx, qx), Vy = fma_(w, my, qy);
-    // u = k V, k = 2 / (A + sqrt(A^2 + 2 b |V|)), A = eps rho + a/2; |u| = k |V|
-    const float A = S + q.ha;
-    const float t = q.hb * sqroot(fma_(Vx, Vx, Vy * Vy));
-    const float Ah = 0.5f * A;
-    const float k = rcp(Ah + sqroot(fma_(Ah, Ah, t)));
+    const float qx = fma_(rho, q.gx, ph.Gx), qy = fma_(rho, q.gy, ph.Gy);
+    const float Vx = fma_(wv, mx, qx), Vy = fma_(wv, my, qy);
+    // u = k V, k = 1 / (A + sqrt(A^2 + b |V|)), A = eps rho + a/2; |u| = k |V|
+    const float A = fma_(0.5f, q.a, S);
+    const float t = q.b * sqroot(fma_(Vx, Vx, Vy * Vy));
+    const float k = rcp(A + sqroot(fma_(A, A, t)));
     const float ux = k * Vx, uy = k * Vy;
-    const float dh = fma_(k, t, q.ha);            // half the drag
+    const float drag = fma_(k, t, q.a);
+    const float Tx = fma_(-drag, ux, qx), Ty = fma_(-drag, uy, qy);
     const float hS = ph.omh * S;
-    const float hx = fma_(hS, ux, ph.P2 * fma_(-dh, ux, qx));
-    const float hy = fma_(hS, uy, ph.P2 * fma_(-dh, uy, qy));
+    const float hx = fma_(ph.omh, fma_(S, ux, -Tx), Tx);
+    const float hy = fma_(ph.omh, fma_(S, uy, -Ty), Ty);
     const float X = ux * hx, Y = uy * hy, XY = X + Y;
-    const float K0 = fma_(-3.0f, XY, ph.om * dS);
+    const float K0 = fma_(-3.0f, XY, ph.omega * dS);
     const float bs = fma_(9.0f, XY, K0), C = fma_(ux, hy, uy * hx);
     const float tx = 3.0f * fma_(hS, ux, hx), ty = 3.0f * fma_(hS, uy, hy);
     g[0] = fma_(ph.omc, g[0], K0);
@@ -1605,7 +1606,7 @@ __device__ __forceinline__ void tb_wave(const S *__restrict__ fin, S *__restrict
     const bool up = tb_turns<S, NS, BXA, WY>() && (chunk & 1);
     Phys<R> ph = ph0;
     if (up) {
-        ph.Ghy = -ph.Ghy;
+        ph.Gy = -ph.Gy;
         ph.wb = ph0.wt;
         ph.wt = ph0.wb;
     }
@@ -3597,19 +3598,11 @@ Phys<R> make_phys(const lbm_vans_params *p)
         ph.rin[i] = cx[i] > 0 ? static_cast<R>(wt[i] * (p->rho_in * pin - rho_ref)) : R(0);
         ph.rout[i] = cx[i] < 0 ? static_cast<R>(wt[i] * (p->rho_out * pout - rho_ref)) : R(0);
     }
-    // omega of the multi-step passes; in FP32 rounded to a multiple of 2^-23 (its own spacing from 1
-    // on), so that 1 - omega and 2 - omega hold no rounding of their own
-    double om = 1.0 / p->tau;
-    if (std::is_same_v<R, float>)
-        om = om >= 0.5 ? std::nearbyint(om * 8388608.0) / 8388608.0
-                       : static_cast<double>(static_cast<float>(om));
-    ph.om = static_cast<R>(om);
+    // of the omega that the steps hold (1 - omega is exact for it up to tau = 2)
+    const double om = static_cast<double>(ph.omega);
     ph.omc = static_cast<R>(1.0 - om);
     ph.omc2 = static_cast<R>(0.5 * (1.0 - om));
     ph.omh = static_cast<R>(0.5 * om);
-    ph.P2 = static_cast<R>(2.0 - om);
-    ph.Ghx = static_cast<R>(0.5 * p->G[0]);
-    ph.Ghy = static_cast<R>(0.5 * p->G[1]);
     ph.c2 = R(0.5) * ph.rho0;
     ph.reservoir = 0;
     ph.inout = p->bc_x == LBM_BC_INOUT;
