@@ -2075,7 +2075,10 @@ void k_sweep_tile(const S *__restrict__ fin, S *__restrict__ fout, const R *__re
 // that is where every row starts on a vector's boundary).  One
 // node per lane and the FP64 sums in every call / now: 4096^2 FP32 315 / 155 us with the
 // diagnostics and 327 / 165 (5.7 TB/s) without, after four-step passes; 8192^2 FP16 1310 /
-// 420, 2048^2 FP64 122 / 88.
+// 420, 2048^2 FP64 122 / 88.  Where the widest vectors would leave compute units without a tile
+// a call is bound by one wave's latency, and one node per lane is the faster: us, widest / one,
+// FP16 250 x 131 5.85 / 3.96, 61 x 40 6.0 / 3.7, 513 x 300 6.3 / 4.7, FP32 250 x 131 5.5 / 3.7,
+// FP64 64 x 32 4.5 / 3.7.
 template <typename S, typename R, int V, bool WX, bool WY, bool DIAG>
 __global__ __launch_bounds__(NTHREADS) void k_moments(const S *__restrict__ fin,
                                                       const R *__restrict__ eps, Geo g,
@@ -3393,6 +3396,8 @@ struct lbm_vans_handle {
                             // (choose_tile); tile_ns 0: this lattice does not take it
     bool tile_on;           // lbm_vans_step takes the tile kernel
     bool tile_fwd;          // ... or would if it recorded nothing (the gradient's forward)
+    bool narrow;            // the read-out takes one node per lane: the widest vectors would
+                            // leave compute units without a tile
     bool tile_one;          // ... also for a launch of one step (one_step_tiles)
     void *scratch;          // device address of the library-held gradient workspace on the
                             // handle's device (lbm_vans_grad_static)
@@ -4176,6 +4181,7 @@ int lbm_vans_init(const lbm_vans_params *p, const void *eps, void *work, size_t 
     h->stream = static_cast<hipStream_t>(stream);
     h->g = make_geo(p);
     h->vec = sweep_vec(p, ncu);
+    h->narrow = make_geo(p, sweep_vmax(p->storage), 1).ntiles < ncu;
     h->gs = make_geo(p, h->vec, sweep_rows_of(p->storage));
     h->ntiles = h->g.ntiles;
     h->pop_bytes = L.pop;
@@ -4372,17 +4378,19 @@ int lbm_vans_moments(lbm_vans_handle *h, void *eps_rho, void *rho, void *ux, voi
                      double *diag)
 {
     if (!h) return fail(LBM_VANS_EINVAL, "handle is NULL");
-    const Geo gm = make_geo(&h->p, sweep_vmax(h->p.storage), 1);   // at most h->ntiles tiles
+    // (at most h->ntiles tiles)
+    const Geo gm = make_geo(&h->p, h->narrow ? 1 : sweep_vmax(h->p.storage), 1);
     int rc = with_types(h->p.storage, [&](auto *sp, auto *rp) {
         using S = std::remove_pointer_t<decltype(sp)>;
         using R = std::remove_pointer_t<decltype(rp)>;
         Phys<R> ph = make_phys<R>(&h->p);
         ph.reservoir = res_on(&h->p, h->n);
-        constexpr int V = sizeof(S) == 8 ? 2 : 4;
         R *const out[4] = {(R *)eps_rho, (R *)rho, (R *)ux, (R *)uy};
-        int vec = h->p.Lx % V == 0;
-        for (const R *o : out) vec = vec && reinterpret_cast<uintptr_t>(o) % (V * sizeof(R)) == 0;
-        auto run = [&](auto wx, auto wy) {
+        auto width = [&](auto v, auto wx, auto wy) {
+            constexpr int V = decltype(v)::value;
+            int vec = h->p.Lx % V == 0;
+            for (const R *o : out)
+                vec = vec && reinterpret_cast<uintptr_t>(o) % (V * sizeof(R)) == 0;
             auto go = [&](auto ker) {
                 hipLaunchKernelGGL(ker, dim3(gm.ntiles), dim3(NTHREADS), 0, h->stream,
                                    (const S *)h->buf[h->cur], (const R *)h->eps, gm, ph, out[0],
@@ -4391,6 +4399,10 @@ int lbm_vans_moments(lbm_vans_handle *h, void *eps_rho, void *rho, void *ux, voi
             constexpr bool WXV = decltype(wx)::value, WYV = decltype(wy)::value;
             if (diag) go(k_moments<S, R, V, WXV, WYV, true>);
             else go(k_moments<S, R, V, WXV, WYV, false>);
+        };
+        auto run = [&](auto wx, auto wy) {
+            if (h->narrow) width(std::integral_constant<int, 1>{}, wx, wy);
+            else width(std::integral_constant<int, sizeof(S) == 8 ? 2 : 4>{}, wx, wy);
         };
         using N0 = std::false_type;
         using Y1 = std::true_type;
