@@ -414,18 +414,22 @@ __device__ __forceinline__ NodeFwd<R> node_forward_m(R dS, R mx, R my, const Eps
         N.rho = N.S * q.ie;
         const R c = third * N.rho;
         const R Qx = fma_(c, q.gex, ph.Gx), Qy = fma_(c, q.gey, ph.Gy);   // Q + G
-        F.Vx = fma_(R(0.5), Qx, mx);
-        F.Vy = fma_(R(0.5), Qy, my);
+        // 2 V, so that neither k / 2 nor 2 b |V| costs the chain an operation
+        const R Vx = fma_(R(2), mx, Qx), Vy = fma_(R(2), my, Qy);
+        const R Vn = sqroot(fma_(Vx, Vx, Vy * Vy)), t = q.b * Vn;
         F.A = fma_(R(0.5), q.a, N.S);
-        F.Vn = sqroot(fma_(F.Vx, F.Vx, F.Vy * F.Vy));
-        F.Rr = sqroot(fma_(F.A, F.A, (R(2) * q.b) * F.Vn));
-        F.k = R(2) * rcp(F.A + F.Rr);
-        N.ux = F.k * F.Vx;
-        N.uy = F.k * F.Vy;
-        F.un = F.k * F.Vn;
-        F.drag = fma_(q.b, F.un, q.a);
+        F.Rr = sqroot(fma_(F.A, F.A, t));
+        const R k = rcp(F.A + F.Rr);
+        N.ux = k * Vx;
+        N.uy = k * Vy;
+        F.drag = fma_(k, t, q.a);
         N.Tx = fma_(-F.drag, N.ux, Qx);
         N.Ty = fma_(-F.drag, N.uy, Qy);
+        F.Vx = R(0.5) * Vx;
+        F.Vy = R(0.5) * Vy;
+        F.Vn = R(0.5) * Vn;
+        F.k = R(2) * k;
+        F.un = k * Vn;
         return F;
     }
     N.S = q.e * ph.rho0 + N.dS;
@@ -500,16 +504,18 @@ __device__ __forceinline__ void collide(R d[9], const Node<R> &N, const Phys<R> 
     const R w0 = R(4) / R(9), w1 = R(1) / R(9), w2 = R(1) / R(36);
     if constexpr (FUSED) {
 #pragma clang fp contract(off)
-        const R uu = fma_(N.ux, N.ux, N.uy * N.uy), uT = fma_(N.ux, N.Tx, N.uy * N.Ty);
+        // (what is late in the chain of operations enters the last one of each value)
+        const R uu = fma_(N.ux, N.ux, N.uy * N.uy);
         const R oS = om * N.S, hS = R(0.5) * oS, P3 = R(3) * P;
-        const R K0 = fma_(-P3, uT, om * fma_(R(-1.5) * N.S, uu, N.dS));
         const R Ax = R(3) * N.ux, Ay = R(3) * N.uy, pBx = P3 * N.Tx, pBy = P3 * N.Ty;
+        const R uT3 = fma_(N.ux, pBx, N.uy * pBy);
+        const R K0 = fma_(om, fma_(R(-1.5) * N.S, uu, N.dS), -uT3);
         auto pair = [&](int i, int j, R A, R pB, R w) {
             const R base = fma_(A, fma_(hS, A, pB), K0), anti = fma_(oS, A, pB);
-            d[i] = fma_(omc, d[i], w * fma_(-hr, D[i], base + anti));
-            d[j] = fma_(omc, d[j], w * fma_(-hr, D[j], base - anti));
+            d[i] = fma_(w, fma_(-hr, D[i], base + anti), omc * d[i]);
+            d[j] = fma_(w, fma_(-hr, D[j], base - anti), omc * d[j]);
         };
-        d[0] = fma_(omc, d[0], w0 * K0);
+        d[0] = fma_(w0, K0, omc * d[0]);
         pair(1, 3, Ax, pBx, w1);
         pair(2, 4, Ay, pBy, w1);
         pair(5, 7, Ax + Ay, pBx + pBy, w2);
@@ -904,10 +910,12 @@ __device__ __forceinline__ void update_node(R d[9], const R (*t)[W], int lyy, in
 // rounded to a multiple of 2^-23 beside an exact 2 - omega, which takes omega's last bit for
 // tau in (1, 2], 11.0 / 8.8 / 4.6 / 4.1; as written 10.2 / 8.2 / 2.9 / 3.9; one-step sweep
 // 12.8 / 11.4 / 4.6 / 4.2.
-// The passes issue 13% fewer vector instructions for it (4096^2 box, four steps: 1.65e8 ->
-// 1.43e8 wave instructions a launch, 91% of the SIMDs' cycles busy) and the four-step pass
-// then runs at the rate of its memory pattern (a copy kernel with the same strips and halo
-// rows: 341 us, the pass 320).  GLUPS, the one-step sweep's form / this one: 4096^2 box
+// The passes issue 14% fewer vector instructions for it (4096^2 box, four steps: 1.65e8 ->
+// 1.42e8 wave instructions a launch: 135 lane instructions per node-step, 109 per update
+// when the recomputed halo is counted; open 2048 x 1024 channel, 12 rows, 152 and 118).  The
+// box's launch (304 us) is near the rate of its memory pattern (a copy kernel with the same
+// strips and halo rows takes 341 us, with turned chunks 325, with 250 columns of a workgroup
+// in step 300) and of its instructions (238 us).  GLUPS, the one-step sweep's form / this one: 4096^2 box
 // 201 / 207, 2048^2 162 / 172, 1024^2 (12 rows) 136 / 147, 4096^2 channel 178 / 182,
 // closed 1003 x 751 box 88 / 93 (6 rows 93 / 103), 1024^2 with walls in y 115 / 127,
 // 16-member ensemble 160 / 168.
@@ -1524,7 +1532,7 @@ constexpr int tb_max_waves()
 // Whether the waves of odd chunks walk their rows bottom to top: the halo rows that two
 // neighbouring chunks both read are then read by both at about the same time and come from
 // HBM once (FP32 four-step pass of the periodic box, the largest lattices: 4096^2 207 / 211
-// GLUPS, copy kernel with its access pattern 341 / 325 us; the channels and the batch do
+// GLUPS, copy kernel with its strips and halo rows 341 / 325 us; the channels and the batch do
 // not gain, 4096^2 channel 182 / 181, ensemble 168 / 162).  Mirrored in y the update is the
 // same arithmetic, to the bit.
 template <typename S, int NS, int BX, bool WY>
@@ -3748,9 +3756,9 @@ void with_bxwy(int bx, bool wy, F &&f)
 }
 
 // Waves of the three-step kernel (lone, or batched) in chunks of `rows` that the
-// chip holds at once: its workgroups per compute unit (registers decide: the
-// periodic FP32 kernel holds two waves per SIMD, the kernels with walls four)
-// times the waves per workgroup and the compute units.
+// chip holds at once: its workgroups per compute unit (the registers they are
+// compiled to decide: periodic FP32 115 to 118, with walls or open ends 122 to
+// 168, FP16 126 to 196) times the waves per workgroup and the compute units.
 int tb3_resident(int storage, int bx, bool wy, int rows, bool batch, long long *out)
 {
     int nb = 0, dev = 0, ncu = 0;
