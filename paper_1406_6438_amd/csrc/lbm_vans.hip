@@ -332,7 +332,9 @@ __device__ __forceinline__ double fma_(double a, double b, double c) { return __
 // others.  Left to itself it fuses the same expression one way or another by what stands
 // beside it (of two products that are added it takes either, and products formed once before
 // a loop stay products), and the kernels that take single steps, the one-step sweep and the
-// tiles, would differ in their last bits.
+// tiles, would differ in their last bits.  Which product is fused shows in sums over all
+// nodes: FP32 diagnostics records move by 2e-9 of their size from one choice to another (by
+// 2e-11 between a run on tiles and one that also takes sweeps of the compiler's choice).
 
 // Darcy and Forchheimer coefficients a = eps^2 nu / K, b = eps^3 F_eps / sqrt(K)
 // of the drag law, one branch-free form for both closures:
@@ -414,22 +416,22 @@ __device__ __forceinline__ NodeFwd<R> node_forward_m(R dS, R mx, R my, const Eps
         N.rho = N.S * q.ie;
         const R c = third * N.rho;
         const R Qx = fma_(c, q.gex, ph.Gx), Qy = fma_(c, q.gey, ph.Gy);   // Q + G
-        // 2 V, so that neither k / 2 nor 2 b |V| costs the chain an operation
+        // 2 V and k / 2 (exact scalings): no doubling of the reciprocal in the chain
         const R Vx = fma_(R(2), mx, Qx), Vy = fma_(R(2), my, Qy);
-        const R Vn = sqroot(fma_(Vx, Vx, Vy * Vy)), t = q.b * Vn;
+        const R Vn = sqroot(fma_(Vx, Vx, Vy * Vy));
         F.A = fma_(R(0.5), q.a, N.S);
-        F.Rr = sqroot(fma_(F.A, F.A, t));
+        F.Rr = sqroot(fma_(F.A, F.A, q.b * Vn));
         const R k = rcp(F.A + F.Rr);
         N.ux = k * Vx;
         N.uy = k * Vy;
-        F.drag = fma_(k, t, q.a);
+        F.un = k * Vn;
+        F.drag = fma_(q.b, F.un, q.a);
         N.Tx = fma_(-F.drag, N.ux, Qx);
         N.Ty = fma_(-F.drag, N.uy, Qy);
         F.Vx = R(0.5) * Vx;
         F.Vy = R(0.5) * Vy;
         F.Vn = R(0.5) * Vn;
         F.k = R(2) * k;
-        F.un = k * Vn;
         return F;
     }
     N.S = q.e * ph.rho0 + N.dS;
@@ -504,22 +506,20 @@ __device__ __forceinline__ void collide(R d[9], const Node<R> &N, const Phys<R> 
     const R w0 = R(4) / R(9), w1 = R(1) / R(9), w2 = R(1) / R(36);
     if constexpr (FUSED) {
 #pragma clang fp contract(off)
-        // (what is late in the chain of operations enters the last one of each value)
-        const R uu = fma_(N.ux, N.ux, N.uy * N.uy);
+        const R uu = fma_(N.ux, N.ux, N.uy * N.uy), uT = fma_(N.ux, N.Tx, N.uy * N.Ty);
         const R oS = om * N.S, hS = R(0.5) * oS, P3 = R(3) * P;
+        const R K0 = fma_(om, fma_(R(-1.5) * N.S, uu, N.dS), -(P3 * uT));
         const R Ax = R(3) * N.ux, Ay = R(3) * N.uy, pBx = P3 * N.Tx, pBy = P3 * N.Ty;
-        const R uT3 = fma_(N.ux, pBx, N.uy * pBy);
-        const R K0 = fma_(om, fma_(R(-1.5) * N.S, uu, N.dS), -uT3);
         auto pair = [&](int i, int j, R A, R pB, R w) {
             const R base = fma_(A, fma_(hS, A, pB), K0), anti = fma_(oS, A, pB);
-            d[i] = fma_(w, fma_(-hr, D[i], base + anti), omc * d[i]);
-            d[j] = fma_(w, fma_(-hr, D[j], base - anti), omc * d[j]);
+            d[i] = fma_(omc, d[i], w * fma_(-hr, D[i], base + anti));
+            d[j] = fma_(omc, d[j], w * fma_(-hr, D[j], base - anti));
         };
-        d[0] = fma_(w0, K0, omc * d[0]);
+        d[0] = fma_(omc, d[0], w0 * K0);
         pair(1, 3, Ax, pBx, w1);
         pair(2, 4, Ay, pBy, w1);
-        pair(5, 7, Ax + Ay, pBx + pBy, w2);
-        pair(6, 8, Ay - Ax, pBy - pBx, w2);
+        pair(5, 7, fma_(R(3), N.uy, Ax), fma_(P3, N.Ty, pBx), w2);
+        pair(6, 8, fma_(R(3), N.uy, -Ax), fma_(P3, N.Ty, -pBx), w2);
         return;
     }
     const R uu = N.ux * N.ux + N.uy * N.uy;
@@ -812,15 +812,18 @@ __device__ __forceinline__ void inout_ends(R d[9], const Node<R> &N, R e0, bool 
     if constexpr (FUSED) {
 #pragma clang fp contract(off)
         if (open_l) {
-            d[3] = fma_(N.S, ph.rin[1], w1 * N.dS);
+            d[3] = fma_(w1, N.dS, N.S * ph.rin[1]);
             if (!wym) d[7] = fma_(N.S, ph.rin[5], w2 * N.dS);
             if (!wyp) d[6] = fma_(N.S, ph.rin[8], w2 * N.dS);
         }
         if (open_r) {
-            const R uu = R(-1.5) * fma_(N.ux, N.ux, N.uy * N.uy);
-            auto q = [&](R eu) { return fma_(fma_(R(4.5), eu, R(3)), eu, uu); };
+            const R uu = fma_(N.ux, N.ux, N.uy * N.uy);
+            auto q = [&](R eu) {
+                return fma_(R(-1.5), uu, fma_(R(3), eu, R(4.5) * eu * eu));
+            };
             const R a = e0 * ph.rho_out, b = e0 * ph.dro;
-            d[1] = w1 * fma_(a, q(-N.ux), b);
+            const R q1 = fma_(N.ux, R(4.5) * N.ux, -(R(3) * N.ux));
+            d[1] = w1 * fma_(a, fma_(R(-1.5), uu, q1), b);
             if (!wym) d[8] = w2 * fma_(a, q(N.uy - N.ux), b);
             if (!wyp) d[5] = w2 * fma_(a, q(-N.ux - N.uy), b);
         }
@@ -1963,9 +1966,10 @@ constexpr int TILE_H = 16;   // rows of a tile (columns: 16 or 32)
 // are grouped into launches.  What depends on the porosity alone is computed once per
 // launch.  FP64 and FP32 storage (S == R: nothing is rounded on the way to memory).  Bound
 // by the latency of a step's chain of operations where a tile has its compute unit to
-// itself (80 x 80 FP64: 1.0 us of the 1.34 us per step), else by the vector instructions of
-// the nodes it recomputes (2048^2 FP64, three steps: 1.6 times the lattice's nodes, 63 us a
-// step against 104 of the one-step sweep, which moves 152 B per node at 6.1 TB/s).
+// itself (80 x 80 FP64: 1.0 us of the 1.25 us per step), else by the loads and instructions of
+// the nodes it recomputes (2048^2 FP64, three steps: 1.52 times the lattice's nodes, 63 us a
+// step, 35 of them VALU, against 104 of the one-step sweep, which moves 152 B per node at 6.1
+// TB/s).
 // all: when not 0, the state of every step s is stored, at fout + s all (elements).
 // h: the rings discarded, ns - 1 or more; (bx, by): the tile.
 template <typename S, typename R, int BX, bool WY, int TW, int TH>
@@ -4239,8 +4243,8 @@ int lbm_vans_init(const lbm_vans_params *p, const void *eps, void *work, size_t 
         delete h;
         return rc;
     }
-    // launch-bound lattices replay their steps as graphs (measured on MI355X, FP64
-    // 80 x 80: see the design notes)
+    // launch-bound lattices replay their steps as graphs (FP64 80 x 80, one step per launch:
+    // 4.66 us a step launched one by one, 4.28 replayed)
     h->use_graphs = h->gs.ntiles < 2 * ncu;
     // the gradient's second stream (default priority) and its events
     hipError_t e = hipStreamCreateWithFlags(&h->stream2, hipStreamNonBlocking);
