@@ -261,8 +261,9 @@ int lbm_vans_diag_read(lbm_vans_handle *h, double *records, int32_t max_records,
 #define LBM_OBJ_OUTLET_FLUX 0
 
 /* Value of the objective (LBM_OBJ_OUTLET_FLUX) for the current state f(., n),
- * computed on the device in FP64 (the value lbm_vans_grad returns as J after
- * the same steps), without a reverse sweep.  J: host double.  Synchronises the
+ * summed on the device in FP64 (the value lbm_vans_grad returns as J after the
+ * same steps, but for the rounding of each node's term, which it computes in the
+ * compute type and lbm_vans_grad in FP64), without a reverse sweep.  J: host double.  Synchronises the
  * stream.  Returns LBM_VANS_ENONFINITE if J is not finite. */
 int lbm_vans_objective(lbm_vans_handle *h, int32_t objective, double *J);
 
