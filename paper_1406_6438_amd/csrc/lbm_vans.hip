@@ -3924,6 +3924,17 @@ int choose_passes(lbm_vans_handle *h)
 int max_pass(const lbm_vans_handle *h);
 int step_pass(const lbm_vans_handle *h) { return h->p.diag_every > 0 ? 1 : max_pass(h); }
 
+// Whether a launch of one step goes on tiles as well, and not to the one-step sweep (the
+// same bits): while both states and the porosity stay in the 256 MB of the last-level cache,
+// where the step is bound by its latency; past that by its bytes, and the sweep's full-width
+// loads are the faster.  Microseconds, sweep / one-step tile: FP64 80 x 80 5.2 / 4.7, 512^2 8.6
+// / 7.8, 1024^2 30 / 26, 1200^2 (219 MB) 44 / 34, 1300^2 (257 MB) 48 / 54, 2048^2 104 / 151;
+// FP32 1024^2 16 / 14, 1800^2 (246 MB) 59 / 48, 2048^2 (319 MB) 54 / 62, 4096^2 207 / 269.
+bool one_step_tiles(long long nodes, int storage)
+{
+    return nodes * 19 * static_cast<long long>(elem_bytes(storage)) <= 256'000'000LL;
+}
+
 // Tile kernel: FP64 and FP32 lattices, unless the caller asked for a kernel of another kind
 // (steps_per_pass, pass_rows, sweep_vec).  lbm_vans_step takes it where a pass takes one
 // step (FP64; FP32 lattices too small for the multi-step passes; runs that record
@@ -3942,17 +3953,6 @@ int step_pass(const lbm_vans_handle *h) { return h->p.diag_every > 0 ? 1 : max_p
 //   4.60 (one-step sweep 3.80) / 1.36 (5), 400 x 200 4.69 / 1.76, 640 x 320 4.87 / 2.81, 1024
 //   x 512 6.75 / 5.15, 1024^2 9.19 / 8.76; walls in y alone 512^2 3.77 / 2.94, 1024^2 7.79 /
 //   7.51, 2048^2 26.7 / 31.6.
-// Whether a launch of one step goes on tiles as well, and not to the one-step sweep (the
-// same bits): while both states and the porosity stay in the 256 MB of the last-level cache,
-// where the step is bound by its latency; past that by its bytes, and the sweep's full-width
-// loads are the faster.  Microseconds, sweep / one-step tile: FP64 80 x 80 5.2 / 4.7, 512^2 8.6
-// / 7.8, 1024^2 30 / 26, 1200^2 (219 MB) 44 / 34, 1300^2 (257 MB) 48 / 54, 2048^2 104 / 151;
-// FP32 1024^2 16 / 14, 1800^2 (246 MB) 59 / 48, 2048^2 (319 MB) 54 / 62, 4096^2 207 / 269.
-bool one_step_tiles(long long nodes, int storage)
-{
-    return nodes * 19 * static_cast<long long>(elem_bytes(storage)) <= 256'000'000LL;
-}
-
 void choose_tile(lbm_vans_handle *h, int ncu)
 {
     const lbm_vans_params *p = &h->p;
@@ -4108,12 +4108,12 @@ int launch_tile(lbm_vans_handle *h, const void *src, void *dst, int64_t n, int n
 }
 
 // Whether the gradient's recomputed states, and its forward where the handle's steps do
-// (tile_fwd), come from the tile kernel, and in FP64 its reverse steps from the reverse tiles.  Not for FP64 lattices above 2^19 nodes, where the recompute and
-// the reverse step beside it on the other stream contend for the FP64 units and the rings'
-// arithmetic costs more than the bytes saved (us per step of the whole gradient, one-step
-// launches and rows / tiles: 512 x 300 29.9 / 20.8, 1024 x 512 60.3 / 57.2, 1024^2 109.6 /
-// 110.4, 2048 x 1024 220 / 224, with the reverse alone on tiles 221 / 238; FP32 2048 x 1024
-// 118 / 115, 4096 x 2048 471 / 461).
+// (tile_fwd), come from the tile kernel, and in FP64 its reverse steps from the reverse tiles.
+// Not for FP64 lattices above 2^19 nodes, where the recompute and the reverse step beside it on
+// the other stream contend for the FP64 units and the rings' arithmetic costs more than the bytes
+// saved (us per step of the whole gradient, one-step launches and rows / tiles: 512 x 300 29.9 /
+// 20.8, 1024 x 512 60.3 / 57.2, 1024^2 109.6 / 110.4, 2048 x 1024 220 / 224, with the reverse
+// alone on tiles 221 / 238; FP32 2048 x 1024 118 / 115, 4096 x 2048 471 / 461).
 bool grad_tiles(const lbm_vans_handle *h)
 {
     return h->tile_ns && (h->p.storage != LBM_F64 ||
